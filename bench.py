@@ -41,7 +41,8 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 METRIC = "MoE-layer µs + tokens/s at 1 GPU; HBM GB/s & MFMA util vs peak"
 # sources of the megakernel: a traffic figure measured on other sources is stale
 KERNEL_SOURCES = ("paper_2609_21483_amd/csrc/forward.hip", "paper_2609_21483_amd/csrc/gemm.h",
-                  "paper_2609_21483_amd/csrc/common.h", "paper_2609_21483_amd/csrc/kernels.h")
+                  "paper_2609_21483_amd/csrc/common.h", "paper_2609_21483_amd/csrc/kernels.h",
+                  "paper_2609_21483_amd/csrc/sched.h")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "megakernel_traffic.json")
 TOL = 2e-2  # max|y - y_ref| <= TOL * max|y_ref| over the checked rows
 

@@ -158,10 +158,10 @@ struct moe_handle {
   moe_calib calib{};
   DevCalib dcal{};
   moe_ws_layout lay{};
-  size_t off_calib = 0, off_blk_cnt = 0, off_blk_off = 0, off_blk_bad = 0, off_rbnd = 0, off_ctl[2] = {0, 0};
+  size_t off_calib = 0, off_blk_cnt = 0, off_blk_off = 0, off_blk_bad = 0, off_rbnd = 0, off_uacc = 0, off_done = 0, off_ctl[2] = {0, 0};
   size_t off_part = 0;
   size_t off_gate = 0;  // the gate's scratch (gate_layout)
-  size_t off_sched = 0;  // schedule images, one per K option (sched_build_kernel)
+  size_t off_sched = 0;  // schedule images, one per K option, and the stored plan (the table builder's)
   uint32_t calib_gen = 1;  // bumped by every moe_set_calib (a stored plan of an older table is stale)
   char* ws = nullptr;
   size_t ws_bytes = 0;
@@ -194,7 +194,7 @@ size_t out_rows(const moe_config& c) {
 
 moe_status validate_cfg(const moe_config* c) {
   if (!c) return fail(MOE_ERR_INVALID_ARG, "config is NULL");
-  if (c->n_src_ranks < 1 || c->n_src_ranks > 64) return fail(MOE_ERR_INVALID_ARG, "n_src_ranks must be in [1, 64]");
+  if (c->n_src_ranks < 1 || c->n_src_ranks > MAX_R) return fail(MOE_ERR_INVALID_ARG, "n_src_ranks must be in [1, %d]", MAX_R);
   if (c->tokens_per_rank < 1) return fail(MOE_ERR_INVALID_ARG, "tokens_per_rank must be >= 1");
   long long T = (long long)c->n_src_ranks * c->tokens_per_rank;
   if (T > (1 << 22)) return fail(MOE_ERR_UNSUPPORTED, "T = %lld tokens exceeds 2^22", T);
@@ -321,6 +321,8 @@ void compute_layout(moe_handle* h) {
   h->off_blk_off = take(sizeof(int32_t) * (size_t)h->nblk * El);
   h->off_blk_bad = take(sizeof(int32_t) * (size_t)h->nblk);
   h->off_rbnd = take(sizeof(int32_t) * (size_t)El * (R + 1));
+  h->off_uacc = take(sizeof(int32_t) * (size_t)R);
+  h->off_done = take(sizeof(int32_t));
   h->off_ctl[0] = take(sizeof(int32_t) * (size_t)h->ctl_words);
   h->off_ctl[1] = take(sizeof(int32_t) * (size_t)h->ctl_words);
   h->arows = a_rows(c);
@@ -340,6 +342,15 @@ moe_status need_ws(moe_handle* h) {
   if (!h) return fail(MOE_ERR_INVALID_ARG, "handle is NULL");
   if (!h->ws) return fail(MOE_ERR_STATE, "no workspace bound (moe_set_workspace)");
   return MOE_OK;
+}
+
+// Movement units: as many as there are wavefronts on the workers (a whole unit
+// per wavefront while every worker still moves rows), at most DT / CT tokens
+// each.
+void move_units(const moe_handle* h, int* dt, int* ct) {
+  const int per = h->T / (h->N * (FNTH / WAVE));
+  *dt = per < 1 ? 1 : (per > DT ? DT : per);
+  *ct = per < 1 ? 1 : (per > CT ? CT : per);
 }
 
 TableArgs table_args(moe_handle* h, const int32_t* topk_idx) {
@@ -366,9 +377,20 @@ TableArgs table_args(moe_handle* h, const int32_t* topk_idx) {
   a.E = h->cfg.n_experts;
   a.e0 = h->cfg.first_local_expert;
   a.El = h->cfg.n_local_experts;
+  a.uniq_acc = at<int32_t>(h, h->off_uacc);
+  a.done = at<int32_t>(h, h->off_done);
+  a.sched = at<int32_t>(h, h->off_sched);
+  a.calib = at<DevCalib>(h, h->off_calib);
+  a.calib_gen = h->calib_gen;
+  a.cb = NTH;
   a.nblk = h->nblk;
   a.S = h->cfg.n_shared_experts;
-  a.tiles_per_row_tile = h->nt0 + h->nt1 * h->nsplit;
+  a.nt0 = h->nt0;
+  a.g1 = h->nt1 * h->nsplit;
+  move_units(h, &a.dt, &a.ct);
+  a.H = h->cfg.hidden;
+  a.F = h->cfg.ffn;
+  a.N = h->N;
   return a;
 }
 
@@ -409,14 +431,7 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
   a.nt0 = h->nt0;
   a.nt1 = h->nt1;
   a.nsplit = h->nsplit;
-  // movement units: as many as there are wavefronts on the workers (a whole
-  // unit per wavefront while every worker still moves rows), at most DT / CT
-  // tokens each
-  {
-    const int per = h->T / (h->N * (FNTH / WAVE));
-    a.dt = per < 1 ? 1 : (per > DT ? DT : per);
-    a.ct = per < 1 ? 1 : (per > CT ? CT : per);
-  }
+  move_units(h, &a.dt, &a.ct);
   a.xmax = h->xmax;
   a.mt_max = h->mt_max;
   a.ctl_words = h->ctl_words;
@@ -669,12 +684,16 @@ moe_status moe_pack_weights(moe_handle* h, const uint16_t* w1, const uint16_t* w
 // (the routing's last kernel did it on the ids it chose).
 static moe_status launch_tables(moe_handle* h, const int32_t* topk_idx, hipStream_t s, bool counted) {
   TableArgs a = table_args(h, topk_idx);
-  if (!counted) tab_count_kernel<<<h->nblk, NTH, 0, s>>>(a);
-  tab_scan_kernel<<<1, TAB_SCAN_THREADS, 0, s>>>(a);
-  tab_perm_kernel<<<h->nblk, NTH, 0, s>>>(a);
-  tab_finalize_kernel<<<1, NTH, 0, s>>>(a);
-  // the launches' schedules for every chunk option, from these tables
-  sched_build_kernel<<<KOPT, FNTH, 0, s>>>(fwd_args(h, nullptr, topk_idx, nullptr, nullptr, nullptr, MOE_MODE_DYNAMIC, nullptr));
+  if (h->T <= TAB_TB) {
+    tab_build_kernel<TAB_TB, true><<<1, TAB_TB + WAVE, 0, s>>>(a);
+  } else if (h->T <= TAB_ONE_T) {
+    tab_build_kernel<TAB_ONE_T, true><<<1, TAB_ONE_T + WAVE, 0, s>>>(a);
+  } else {
+    if (!counted) tab_count_kernel<<<h->nblk, NTH, 0, s>>>(a);
+    a.scanned = (long long)a.nblk * a.El > TAB_SUM_MAX ? 1 : 0;
+    if (a.scanned) tab_scan_kernel<<<1, TAB_SCAN_THREADS, 0, s>>>(a);
+    tab_build_kernel<TAB_TB, false><<<(h->T + TAB_TB - 1) / TAB_TB, TAB_TB + WAVE, 0, s>>>(a);
+  }
   HIP_TRY(hipGetLastError());
   h->tables_from = topk_idx;
   return MOE_OK;
@@ -707,7 +726,7 @@ moe_status moe_route(moe_handle* h, const uint16_t* x, const uint16_t* wg, const
   // the chain counter goes to the layer's stats (word ST_CANDS, reported)
   bind_gate(g, h->ws + h->off_gate, gate_layout(g.T, g.H, g.E), at<int32_t>(h, h->lay.stats));
   const TableArgs ta = table_args(h, topk_idx);
-  st = launch_gate(g, s, &ta);
+  st = launch_gate(g, s, h->T > TAB_ONE_T ? &ta : nullptr);
   if (st != MOE_OK) return st;
   return launch_tables(h, topk_idx, s, true);
 }

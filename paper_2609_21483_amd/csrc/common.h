@@ -36,6 +36,7 @@ constexpr int CT = 4;           // most tokens per combine unit (one wavefront)
 
 constexpr int MAX_EL = 64;      // local experts
 constexpr int MAX_S = 8;        // shared experts
+constexpr int MAX_R = 64;       // source ranks
 constexpr int MAX_SEG = MAX_EL + MAX_S;
 constexpr int MAX_K = 8;        // chunk count limit
 constexpr int NLVL = 1;        // readiness levels of the routed row tiles of a stage

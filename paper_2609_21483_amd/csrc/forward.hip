@@ -21,23 +21,16 @@
 #include "common.h"
 #include "gemm.h"
 #include "kernels.h"
+#include "sched.h"
 
 namespace moe {
 
 constexpr int NWF = FNTH / WAVE;  // waves per forward workgroup
 
-// ===========================================================================
-// Schedule of one launch for chunk count K (struct Sched, kernels.h): built
-// once per K option by sched_build_kernel when the routing tables are, and
-// copied into each workgroup's LDS by its prologue.
-// ===========================================================================
-
-
 struct Scratch {
   int bc[8];
   DevCalib cal;                                        // the calibration table, staged by the prologue
   int st[ST_WORDS];                                    // routing stats (ST_*), staged by the prologue
-  int part[NWF];
   int wsl[NWF][WAVE];    // per wavefront: slots of its unit's (token, j) pairs
   int wact[NWF][DT];     // per wavefront: its dispatch unit's tokens that have a local slot
   int dexh;              // every dispatch unit has been claimed (seen by this workgroup)
@@ -46,148 +39,12 @@ struct Scratch {
   float wwt[NWF][WAVE];  // per wavefront: their weights
 };
 
-// block-wide exclusive scan of n ints in LDS (all threads call): each thread
-// sums a contiguous run, wavefront shuffles scan the run sums, then the runs
-// are rewritten with their offsets
-__device__ __forceinline__ void block_exscan(int* v, int n, int* part) {
-  const int tid = threadIdx.x;
-  const int lane = tid & (WAVE - 1), wave = tid / WAVE;
-  const int per = (n + FNTH - 1) / FNTH;
-  const int b = tid * per, e = min(n, b + per);
-  int mine = 0;
-  for (int i = b; i < e; ++i) mine += v[i];
-  int x = mine;
-#pragma unroll
-  for (int d = 1; d < WAVE; d <<= 1) {
-    int y = __shfl_up(x, d, WAVE);
-    if (lane >= d) x += y;
-  }
-  if (lane == WAVE - 1) part[wave] = x;
-  __syncthreads();
-  int run = x - mine;
-  for (int w = 0; w < wave; ++w) run += part[w];
-  for (int i = b; i < e; ++i) { int t = v[i]; v[i] = run; run += t; }
-  __syncthreads();
-}
-
-// XCD-aware tile queues.  A tile's weight slab is its GEMM0 column tile, or
-// its GEMM1 (column tile, split) pair; the tiles of one slab share the slab's
-// weights, so they are queued for one XCD (slab class = slab mod NXCD) and
-// read them from that XCD's L2.  Stage = (chunk, phase) in DAG order; each
-// stage has one queue per class, the row tile fastest within a slab.
+// slabs of a phase (see class_slabs)
 __device__ __forceinline__ int phase_slabs(const FwdArgs& a, int ph) { return ph == 0 ? a.nt0 : a.nt1 * a.nsplit; }
-__device__ __forceinline__ int class_slabs(int ns, int x) { return ns > x ? (ns - x + NXCD - 1) / NXCD : 0; }
 
-// Readiness levels order the row tiles of a stage by when their inputs can be
-// complete.  Dispatch writes a local expert's rows in token order, so row
-// tile mt of a segment of `rows` rows is complete once the fraction
-// min((mt + 1) * BM, rows) / rows of the segment is written; its level is
-// that fraction rounded up to a multiple of 1/NLVL (1..NLVL).  Shared-expert
-// rows are read straight from x: level 0, ready at launch.  With every
-// worker copying rows at the start, the routed row tiles all complete at
-// nearly the same time, and one routed level (NLVL = 1) measures fastest:
-// it keeps the row tiles of one expert and weight slab together, so the
-// tiles running on an XCD share that slab in its L2 (finer levels spread the
-// first claims over every expert and slab and fetch the weights several
-// times over).
-__device__ __forceinline__ int tiles_upto(int rows, int L) {  // routed tiles at level <= L
-  const int nmt = (rows + BM - 1) / BM;
-  if (L <= 0) return 0;
-  if (L >= NLVL) return nmt;
-  return min(nmt, (int)(((long long)L * rows) / ((long long)NLVL * BM)));
-}
-__device__ __forceinline__ int level_lo(int rows, bool shared, int L) {  // first row tile of level L
-  return shared ? 0 : tiles_upto(rows, L - 1);
-}
-__device__ __forceinline__ int level_tiles(int rows, bool shared, int L) {
-  if (shared) return L == 0 ? (rows + BM - 1) / BM : 0;
-  return tiles_upto(rows, L) - tiles_upto(rows, L - 1);
-}
-
-// Queue order of the stages (chunk, phase) of a K-chunk schedule, skewed by
-// one chunk: (0,G0), (1,G0), (0,G1), (2,G0), (1,G1), ..., (K-1,G0), (K-2,G1),
-// (K-1,G1).  Workers reach chunk q's GEMM1 tiles only after claiming chunk
-// q+1's GEMM0 tiles, which depend on dispatch alone, so chunk q's last GEMM0
-// tiles finish while those run instead of holding up a worker at every chunk
-// boundary.  Returns chunk << 1 | phase.
-__device__ __forceinline__ int stage_qph(int s, int K) {
-  if (s == 0) return 0;
-  if (s >= 2 * K - 1) return ((K - 1) << 1) | 1;
-  const int j = (s + 1) >> 1;
-  return (s & 1) ? (j << 1) : (((j - 1) << 1) | 1);
-}
-
-// The schedule for K in S (all threads call; sched_build_kernel's workgroups).
-// sub, rof: the chunk sub-offset and row-map tables (a.sub_off, a.row_off)
-__device__ __forceinline__ void build_sched(const FwdArgs& a, const int* sub, const int* rof, Sched& S, Scratch& W,
-                                            int K) {
-  const int tid = threadIdx.x;
-  const int ki = kopt_index(K);
-  const int nseg = a.El + a.S;
-  const int g1tiles = a.nt1 * a.nsplit;  // GEMM1 tiles per row tile
-  // chunk token boundaries ceil(q T / K); K is 1, 2, 4 or 8
-  if (tid <= K) S.bnd[tid] = (int)(((long long)tid * a.T + K - 1) >> __builtin_ctz((unsigned)K));
-  if (tid == 0) {
-    S.K = K;
-    S.nseg = nseg;
-    S.G = K * 2 * nseg;
-    S.n_comb = ceil_div(a.T, a.ct);
-    S.n_disp = ceil_div(a.T, a.dt);
-  }
-  __syncthreads();
-  for (int v = tid; v < K * nseg; v += FNTH) {
-    int q = v / nseg, seg = v % nseg;
-    int rows, sbase, arow0;
-    const int row0 = rof[((size_t)ki * nseg + seg) * SUBW + q];
-    if (seg < a.El) {
-      const int* so = sub + ((size_t)ki * a.El + seg) * SUBW;
-      sbase = so[q];
-      rows = so[q + 1] - so[q];
-      arow0 = row0;
-    } else {
-      int t0 = S.bnd[q], t1 = min(S.bnd[q + 1], a.Tr);
-      rows = max(0, t1 - t0);
-      sbase = t0;
-      arow0 = t0;
-    }
-    S.rows[v] = rows;
-    S.row0[v] = row0;
-    S.sbase[v] = sbase;
-    S.arow0[v] = arow0;
-    S.mb[v] = ceil_div(rows, BM);
-  }
-  __syncthreads();
-  for (int gi = tid; gi < S.G; gi += FNTH) {
-    int q = gi / (2 * nseg), ph = (gi / nseg) & 1, seg = gi % nseg;
-    S.gstart[gi] = S.mb[q * nseg + seg] * (ph ? g1tiles : a.nt0);
-  }
-  if (tid == 0) S.gstart[S.G] = 0;
-  __syncthreads();
-  for (int v = tid; v < 2 * K * NXCD; v += FNTH) {
-    const int stage = v / NXCD, x = v % NXCD, qp = stage_qph(stage, K), q = qp >> 1;
-    const int nsx = class_slabs(phase_slabs(a, qp & 1), x);
-    int n = 0;
-    for (int seg = 0; seg < nseg; ++seg) n += nsx * ceil_div(S.rows[q * nseg + seg], BM);
-    S.ncls[stage][x] = n;
-  }
-  for (int v = tid; v < K * (NLVL + 1); v += FNTH) {
-    const int q = v / (NLVL + 1), L = v % (NLVL + 1);
-    int n = 0;
-    for (int seg = 0; seg < nseg; ++seg) n += level_tiles(S.rows[q * nseg + seg], seg >= a.El, L);
-    S.lvl[q][L] = n;
-  }
-  __syncthreads();
-  if (tid < K)
-    for (int L = 1; L <= NLVL; ++L) S.lvl[tid][L] += S.lvl[tid][L - 1];
-  block_exscan(S.mb, K * nseg, W.part);
-  block_exscan(S.gstart, S.G + 1, W.part);
-  if (tid == 0) S.n_comp = S.gstart[S.G];
-  __syncthreads();
-}
-
-// A launch's schedule for chunk count K: the stored image (built by
-// sched_build_kernel when the routing tables were) copied into S after the
-// plan fields, which it leaves alone.  All threads call; ends with a barrier.
+// A launch's schedule for chunk count K: the stored image (struct Sched,
+// built with the routing tables) copied into S after the plan fields, which
+// it leaves alone.  All threads call; ends with a barrier.
 __device__ __forceinline__ void load_sched(const FwdArgs& a, Sched& S, int K) {
   const int32_t* src = a.sched + (size_t)kopt_index(K) * SCHED_WORDS;
   int* dst = reinterpret_cast<int*>(&S);
@@ -845,82 +702,6 @@ __device__ __forceinline__ bool arrive_and_reduce(const FwdArgs& a, const Sched&
 // Prologue: the routing-derived workload and the plan (sections 3.1-3.3),
 // computed redundantly by every workgroup from a small read of the stats.
 // ===========================================================================
-// sub: the chunk sub-offset tables staged in LDS (see moe_megakernel); the
-// calibration table is staged here, in the same round trip.
-// Wavefront argmin of (t, i) (lanes with i < 0 hold no point): the smallest
-// t, the lowest i among equal ones, with n carried along; lane 0 ends with
-// the result.  DPP exchanges within each row of 16 lanes (xor 1, xor 2, then
-// the half-row and row mirrors, each pairing the lanes of two disjoint halves),
-// then the four rows' results through readlane.  The order of the minimum
-// with its index tie-break is total, so the pairing order does not matter.
-__device__ __forceinline__ void argmin_take(double& t, int& i, int& n, double t2, int i2, int n2) {
-  if (i2 >= 0 && (i < 0 || t2 < t || (t2 == t && i2 < i))) {
-    t = t2;
-    i = i2;
-    n = n2;
-  }
-}
-template <int CTRL>
-__device__ __forceinline__ void argmin_dpp_step(double& t, int& i, int& n) {
-  const uint64_t b = (uint64_t)__builtin_bit_cast(uint64_t, t);
-  const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
-  const int i2 = __builtin_amdgcn_mov_dpp(i, CTRL, 0xF, 0xF, false);
-  const int n2 = __builtin_amdgcn_mov_dpp(n, CTRL, 0xF, 0xF, false);
-  const double t2 = __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-  argmin_take(t, i, n, t2, i2, n2);
-}
-__device__ __forceinline__ void wave_argmin(double& t, int& i, int& n) {
-  argmin_dpp_step<0xB1>(t, i, n);   // quad_perm [1, 0, 3, 2]
-  argmin_dpp_step<0x4E>(t, i, n);   // quad_perm [2, 3, 0, 1]
-  argmin_dpp_step<0x141>(t, i, n);  // row_half_mirror
-  argmin_dpp_step<0x140>(t, i, n);  // row_mirror
-  const uint64_t b = (uint64_t)__builtin_bit_cast(uint64_t, t);
-#pragma unroll
-  for (int r = 1; r < 4; ++r) {
-    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, 16 * r);
-    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 16 * r);
-    const int i2 = __builtin_amdgcn_readlane(i, 16 * r);
-    const int n2 = __builtin_amdgcn_readlane(n, 16 * r);
-    argmin_take(t, i, n, __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo), i2, n2);
-  }
-}
-
-// The cost model's plan on the first wavefront (all 64 lanes call; lane 0
-// ends with it in p): Eq 15 at every grid point, one point per lane, with its
-// steal count (Eq 11-14) alongside; Eq 16 by a wavefront argmin in the host
-// model's order (c ascending, then K): the smallest T_total, the lowest grid
-// index among equal ones, which is the first strict minimum of the host's
-// scan.  W.cal and W.st hold the calibration table and the routing stats.
-__device__ __forceinline__ void model_plan(const FwdArgs& a, const Scratch& W, moe_plan& p) {
-  const int tid = threadIdx.x;
-  double wc, wd, wb;
-  cm_volumes(W.st, a.H, a.F, a.S * a.Tr, W.cal.literal, &wc, &wd, &wb);
-  const int nk = W.cal.n_k, npt = W.cal.n_c * nk;
-  double best = 0.0;
-  int bi = -1;
-  for (int i = tid; i < npt; i += WAVE) {
-    const double t = cm_t_total(W.cal, i / nk, i - (i / nk) * nk, wc, wd, wb);
-    if (bi < 0 || t < best) { best = t; bi = i; }
-  }
-  int ns = 0;
-  if (bi >= 0) {
-    long long nt_by_k[MOE_CALIB_MAX_K];
-    for (int j = 0; j < nk; ++j) nt_by_k[j] = W.st[ST_NTK + kopt_index(W.cal.kk[j])];
-    moe_plan q;
-    cm_finish(W.cal, a.N, wc, wd, wb, nt_by_k, bi / nk, bi - (bi / nk) * nk, best, &q);
-    ns = q.n_steal;
-  }
-  wave_argmin(best, bi, ns);
-  if (tid == 0) {
-    p.c = W.cal.c[bi / nk];
-    p.K = W.cal.kk[bi - (bi / nk) * nk];
-    p.n_steal = ns;
-    p.final_all = 1;
-    p.t_pred_s = best;
-  }
-}
-
 __device__ __forceinline__ void prologue_plan(const FwdArgs& a, Sched& S, Scratch& W) {
   const int tid = threadIdx.x;
   StoredPlan sp{};  // thread 0: the stored plan, read in the same round trip
@@ -961,7 +742,7 @@ __device__ __forceinline__ void prologue_plan(const FwdArgs& a, Sched& S, Scratc
   moe_plan p;
   // the plan the routing's last kernel evaluated on these tables, when the
   // calibration has not changed since (W.bc[6]); else evaluated here
-  if (model && !W.bc[6] && tid < WAVE) model_plan(a, W, p);
+  if (model && !W.bc[6] && tid < WAVE) model_plan(W.cal, W.st, a.H, a.F, a.S * a.Tr, a.N, p);
   if (tid == 0) {
     if (model && W.bc[6]) {
       p = sp.p;
@@ -1278,34 +1059,6 @@ __global__ void __launch_bounds__(FNTH, 1) moe_megakernel_stack(StackArgs st) {
 // ===========================================================================
 // Serial baseline: four kernels, each on every CU, no overlap.
 // ===========================================================================
-// The schedule images of the routing tables just built: workgroup ki builds
-// the schedule for K = 2^ki in LDS and stores it.
-__global__ void __launch_bounds__(FNTH, 1) sched_build_kernel(FwdArgs a) {
-  __shared__ Sched S;
-  __shared__ Scratch W;
-  const int ki = blockIdx.x;
-  build_sched(a, a.sub_off, a.row_off, S, W, 1 << ki);
-  const int* src = reinterpret_cast<const int*>(&S);
-  int32_t* dst = const_cast<int32_t*>(a.sched) + (size_t)ki * SCHED_WORDS;  // the images' one writer
-  for (int i = SCHED_IMG0 + threadIdx.x; i < SCHED_WORDS; i += FNTH) dst[i] = src[i];
-  if (ki != 0) return;
-  // the cost model's plan of these tables under the current calibration
-  // (every workgroup of a launch would evaluate the same; a prologue whose
-  // calibration generation differs evaluates it again)
-  const uint32_t* csrc = reinterpret_cast<const uint32_t*>(a.calib);
-  uint32_t* cdst = reinterpret_cast<uint32_t*>(&W.cal);
-  for (int i = threadIdx.x; i < (int)(sizeof(DevCalib) / 4); i += FNTH) cdst[i] = csrc[i];
-  for (int i = threadIdx.x; i < ST_WORDS; i += FNTH) W.st[i] = a.stats[i];
-  __syncthreads();
-  moe_plan p;
-  if (threadIdx.x < WAVE) model_plan(a, W, p);
-  if (threadIdx.x == 0) {
-    StoredPlan* sp = const_cast<StoredPlan*>(stored_plan(a));
-    sp->p = p;
-    sp->gen = a.calib_gen;
-  }
-}
-
 __global__ void __launch_bounds__(FNTH, 1) serial_dispatch_kernel(FwdArgs a) {
   __shared__ Scratch W;
   const int tid = threadIdx.x;

@@ -6,6 +6,8 @@
 
 namespace moe {
 
+struct DevCalib;
+
 struct GateArgs {
   const uint16_t* x;   // [T][H] bf16
   const uint16_t* wg;  // [H][E] bf16
@@ -39,11 +41,20 @@ struct TableArgs {
   int32_t* stats;
   int32_t* blk_cnt;
   int32_t* blk_off;
-  int32_t* blk_bad;    // [nblk] tokens with an invalid or repeated id, per table block
+  int32_t* blk_bad;    // [nblk] tokens with an invalid or repeated id, per count block
   int32_t* rbnd;       // [E_l][R + 1] first slot of each expert at or after each rank boundary
+  int32_t* uniq_acc;   // [R] unique tokens per rank, accumulated by the table blocks (zero between launches)
+  int32_t* done;       // table blocks finished (zero between launches)
   int32_t* err;
-  int T, Tr, R, k, E, e0, El, nblk;
-  int S, tiles_per_row_tile;  // shared experts; GEMM0 + GEMM1 tiles of one row tile (the cost model's tile counts)
+  int32_t* sched;      // [KOPT][SCHED_WORDS] schedule images, then the StoredPlan
+  const DevCalib* calib;
+  uint32_t calib_gen;
+  int T, Tr, R, k, E, e0, El;
+  int cb, nblk;        // tokens per count block (blk_cnt, blk_bad), a power of two <= TAB_TB, and count blocks
+  int scanned;         // blk_off and off hold tab_scan_kernel's result (else the table blocks sum blk_cnt)
+  int S, nt0, g1;      // shared experts; GEMM0 and GEMM1 tiles of one row tile
+  int dt, ct;          // tokens per dispatch and combine unit
+  int H, F, N;         // the cost model's shape and worker count
 };
 
 // One source matrix [rows][cols] per segment, written transposed into a
@@ -84,16 +95,15 @@ struct DevCalib {
 // seg - E_l.  Queue order: chunk, then phase (GEMM0 tiles, then GEMM1 tiles),
 // then segment; inside a group the row tile runs fastest (GEMM1: the split
 // runs fastest, then the row tile).  Everything from K on depends only on the
-// routing tables and the handle, so the routing's last kernel
-// (sched_build_kernel) stores it once per K option as an image that a
-// launch's prologue copies into LDS once its plan has picked K; the plan
-// fields come first and are not part of the image.
+// routing tables and the handle, so the table builder stores it once per K
+// option as an image that a launch's prologue copies into LDS once its plan
+// has picked K; the plan fields come first and are not part of the image.
 struct Sched {
   int c, n_steal, final_all;  // the plan
   int disp0;                  // dispatch units [0, disp0) are owned statically (megakernel)
-  int K, nseg, G;             // chunks, segments, groups = K*2*nseg
-  int n_comp, n_disp, n_comb;
-  int bnd[MAX_K + 1];         // chunk token boundaries ceil(q*T/K)
+  int K, nseg;                // chunks, segments
+  int n_disp, n_comb;         // movement units
+  int bnd[MAX_K + 4];         // chunk token boundaries ceil(q*T/K), q <= K
   // per (chunk q, segment) at index q*nseg + seg
   int rows[MAX_K * MAX_SEG];
   int row0[MAX_K * MAX_SEG];   // first row in Hbuf / O (and in A for local experts), a 32-row group boundary
@@ -101,13 +111,12 @@ struct Sched {
   int arow0[MAX_K * MAX_SEG];  // first row of the GEMM0 A operand (A row or token)
   int mb[MAX_K * MAX_SEG];     // first row-tile id (counter index)
   int lvl[MAX_K][NLVL + 1];    // row tiles of chunk q at readiness level <= L
-  int gstart[MAX_K * 2 * MAX_SEG + 1];
   int ncls[2 * MAX_K][NXCD];   // tiles of stage (chunk, phase) in slab class x
 };
 constexpr int SCHED_WORDS = (int)(sizeof(Sched) / 4);  // int32 words of a stored image slot
 
 // The cost model's plan for the tables the schedule images were built from,
-// evaluated by sched_build_kernel with the calibration of generation `gen`
+// evaluated by the table builder with the calibration of generation `gen`
 // (it follows the images in the workspace).
 struct StoredPlan {
   moe_plan p;
@@ -139,7 +148,7 @@ struct FwdArgs {
   const int32_t* slot;
   const int32_t* sub_off;
   const int32_t* row_off;  // [KOPT][E_l + S][SUBW] first row of each (segment, chunk) in A / Hbuf / O
-  const int32_t* sched;    // [KOPT][SCHED_WORDS] schedule images (written by sched_build_kernel), K = 1, 2, 4, 8
+  const int32_t* sched;    // [KOPT][SCHED_WORDS] schedule images (written by the table builder), K = 1, 2, 4, 8
   const int32_t* stats;
   // intermediate buffers
   uint16_t* A;
@@ -292,15 +301,18 @@ __global__ void gate_final_kernel(GateArgs a, TableArgs t);  // EPL >= E / 16 ex
                                                              // tab_count_kernel's step on the chosen ids
 __global__ void tab_count_kernel(TableArgs a);
 __global__ void tab_scan_kernel(TableArgs a);
-__global__ void tab_perm_kernel(TableArgs a);
-__global__ void tab_finalize_kernel(TableArgs a);
+template <int TBN, bool ONE>
+__global__ void tab_build_kernel(TableArgs a);  // TBN tokens per workgroup of TBN + 64 threads; ONE: a single
+                                                // workgroup, which counts for itself
+constexpr int TAB_TB = 512;             // tokens per workgroup of the several-workgroup table builder
+constexpr int TAB_ONE_T = 1024 - 64;    // most tokens of the one-workgroup table builder (1024 threads)
+constexpr int TAB_SUM_MAX = 16384;      // most count words the table blocks sum themselves
 constexpr int TAB_SCAN_THREADS = 1024;  // one workgroup of tab_scan_kernel
 __global__ void zero_i32_kernel(int* p, int n);
 __global__ void pack_transpose_kernel(PackArgs a);
 __global__ void pack_pad_kernel(PadArgs a);
 __global__ void moe_megakernel(FwdArgs a);
 __global__ void moe_megakernel_stack(StackArgs st);
-__global__ void sched_build_kernel(FwdArgs a);  // one workgroup per K option
 __global__ void serial_dispatch_kernel(FwdArgs a);
 __global__ void serial_gemm0_kernel(FwdArgs a);
 __global__ void serial_gemm1_kernel(FwdArgs a);

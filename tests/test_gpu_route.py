@@ -203,3 +203,39 @@ def test_bad_routing_ids_are_flagged(B, Tr, rows):
         assert B.moe_sync_status(hd.h) == B.MOE_OK  # the error word was cleared
     finally:
         hd.close()
+
+
+@pytest.mark.parametrize("R,Tr,E,k,El,S", [
+    (1, 256, 16, 2, 8, 1),       # one workgroup of 256 tokens, full
+    (1, 257, 16, 2, 8, 0),       # the first size of the 1024-token workgroup
+    (4, 256, 128, 8, 64, 2),     # its last
+    (5, 205, 128, 8, 64, 0),     # 1025 tokens: several workgroups, the second nearly empty
+    (2, 2048, 64, 8, 1, 0),      # one local expert
+    (64, 1040, 64, 1, 64, 0),    # more count words than the table blocks sum themselves; 64 ranks
+])
+def test_build_tables_workgroup_edges(B, R, Tr, E, k, El, S):
+    """Sizes where the table builder changes its launch; twice in a row on one
+    workspace, so that the accumulators are seen to be zero again."""
+    shape = W.MoeShape("t", 99, R, Tr, 64, 64, E, k, El, n_shared_experts=S)
+    hd = Handle(B, shape)
+    try:
+        for rep in range(2):
+            idx_ref, _ = W.random_routing(shape.T, E, k, seed=17 + rep, skew=0.8)
+            idx = torch.from_numpy(idx_ref).cuda()
+            B.moe_build_tables(hd.h, idx)
+            assert B.moe_sync_status(hd.h) == B.MOE_OK
+            tab = check_tables(hd, shape, idx_ref)
+        # the row maps and tile counts over them
+        bm, nt0, nt1 = B.moe_tile_geometry(hd.h)
+        rof = hd.view("row_off", 4 * (El + S) * 9).reshape(4, El + S, 9)
+        st = hd.view("stats", 16)
+        for ki, K in enumerate((1, 2, 4, 8)):
+            sub = O.chunk_offsets(tab, shape.T, k, K)
+            bnd = [min((q * shape.T + K - 1) // K, Tr) for q in range(K + 1)]
+            rows = np.array([np.diff(sub[le]) for le in range(El)] + [np.diff(bnd)] * S, np.int64)
+            up = -(-rows // 32) * 32
+            start = np.concatenate([[0], np.cumsum(up.reshape(-1))[:-1]]).reshape(El + S, K)
+            assert np.array_equal(rof[ki, :, :K], start) and not rof[ki, :, K:].any(), K
+            assert st[10 + ki] == int((-(-rows // bm)).sum()) * (nt0 + nt1), K
+    finally:
+        hd.close()
