@@ -157,7 +157,9 @@ typedef struct {
   size_t cnt_rank;    /* int32 [E_l][R] */
   size_t uniq;        /* int32 [R] */
   size_t stats;       /* int32 [16]: X, X_local, X_in, U_local, U_in, bad ids (0-5);
-                         gate candidates (8); GEMM tiles of the layer at
+                         gate candidates (8): the experts whose logits the
+                         filtering gate evaluated, T*k where the gate
+                         evaluates every logit; GEMM tiles of the layer at
                          K = 1, 2, 4, 8 chunks (10-13), written by the table
                          builder for the cost model (section 3.2, Eq 14) */
   size_t plan;        /* moe_plan of the last megakernel launch */
@@ -285,11 +287,12 @@ moe_status moe_route(moe_handle* h, const uint16_t* x, const uint16_t* wg,
  * forbid allocation.  It builds no routing tables (moe_build_tables does).
  * x: bf16 [T][H], wg: bf16 [H][E], logit_bias: fp32 [E] or NULL; writes
  * topk_idx int32 [T][top_k] and topk_w fp32 [T][top_k] as moe_route does.
- * The gate's scratch (its intermediate logits, norms and candidate chains,
- * about E*H*2 + 16*T*E + 16*T bytes) lives in a static device array of
- * MOE_ROUTE_STATIC_SCRATCH_BYTES that each GPU the library runs on holds
- * until the process ends; larger problems are refused with
- * MOE_ERR_UNSUPPORTED (nothing is launched).  Every call on a GPU shares that
+ * The gate's scratch (a padded copy of wg; for large batches of more than 64
+ * experts, intermediate logits, norms and candidate chains) lives in a static
+ * device array of MOE_ROUTE_STATIC_SCRATCH_BYTES that each GPU the library
+ * runs on holds until the process ends; problems of more than about
+ * E*H*2 + 16*T*E + 16*T = 96 MiB are refused with MOE_ERR_UNSUPPORTED (nothing
+ * is launched).  Every call on a GPU shares that
  * GPU's array and leaves its contents behind: calls that overlap on one GPU
  * (other streams, other threads) race, so serialise them.  H must be a
  * multiple of 64 in [64, 16384], E in [1, 512], top_k in [1, min(E, 8)]. */

@@ -39,112 +39,37 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 namespace {
 
-// The gate's scratch: everything its kernels use besides their inputs and
-// outputs (the transposed gate matrix and its row norms, the approximate
-// logits and token norms, the candidate chains and their exact logits, each
-// token's range of chains, and the chain counter in stats word ST_CANDS).
-struct GateLayout {
-  size_t wgt, lt, xn, wn, chg, che, chl, tb, tn, stats, total;
-};
-GateLayout gate_layout(long long T, long long H, long long E) {
-  GateLayout L{};
+// Bytes by which moe_route_topk_static limits its problems (transposed gate,
+// logits, norms and candidate lists of a filtering gate).
+size_t static_route_bytes(long long T, long long H, long long E) {
   size_t o = 0;
-  auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
-  L.wgt = take(sizeof(uint16_t) * (size_t)(E * H));
-  L.lt = take(sizeof(float) * (size_t)(T * E));
-  L.xn = take(sizeof(float) * (size_t)T);
-  L.wn = take(sizeof(float) * (size_t)E);
-  L.chg = take(sizeof(int32_t) * (size_t)(T * E));
-  L.che = take(sizeof(int32_t) * (size_t)(T * E));
-  L.chl = take(sizeof(float) * (size_t)(T * E));
-  L.tb = take(sizeof(int32_t) * (size_t)T);
-  L.tn = take(sizeof(int32_t) * (size_t)T);
-  L.stats = take(sizeof(int32_t) * ST_WORDS);
-  L.total = o;
-  return L;
+  for (size_t bytes : {2 * (size_t)(E * H), 4 * (size_t)(T * E), 4 * (size_t)T, 4 * (size_t)E, 4 * (size_t)(T * E),
+                       4 * (size_t)(T * E), 4 * (size_t)(T * E), 4 * (size_t)T, 4 * (size_t)T, 4 * (size_t)ST_WORDS})
+    o = align_up(o + bytes, 256);
+  return o;
 }
 
-// Points the gate's scratch arguments into `base` laid out by L; the chain
-// counter goes to `stats` (a stats block of ST_WORDS words).
-void bind_gate(GateArgs& g, char* base, const GateLayout& L, int32_t* stats) {
-  g.wgt = reinterpret_cast<uint16_t*>(base + L.wgt);
-  g.lt = reinterpret_cast<float*>(base + L.lt);
-  g.xn = reinterpret_cast<float*>(base + L.xn);
-  g.wn = reinterpret_cast<float*>(base + L.wn);
-  g.ch_g = reinterpret_cast<int32_t*>(base + L.chg);
-  g.ch_e = reinterpret_cast<int32_t*>(base + L.che);
-  g.ch_l = reinterpret_cast<float*>(base + L.chl);
-  g.tok_base = reinterpret_cast<int32_t*>(base + L.tb);
-  g.tok_n = reinterpret_cast<int32_t*>(base + L.tn);
-  g.stats = stats;
-}
-
-// Top-k routing (gate logits, softmax, top-k, renormalisation) on a bound
-// GateArgs: the certified filter's kernels in order on `s`.  tab: the
-// routing tables to start on the chosen ids (their counting step, done by the
-// last kernel), or null.
-moe_status launch_gate(GateArgs& g, hipStream_t s, const TableArgs* tab) {
-  // |L - L~| <= (gamma_{H-1}(2^-24) + gamma_H(2^-23)) * sum_h |x_h w_h|: the
-  // defined recursive fp32 sum and an fp32 accumulation of the MFMA products
-  // allowed twice the unit roundoff; sum |x w| <= ||x|| ||w||; 1% for the norms
-  {
-    const double H = (double)g.H, u = std::ldexp(1.0, -24), u2 = std::ldexp(1.0, -23);
-    const double g1 = (H - 1.0) * u / (1.0 - (H - 1.0) * u), g2 = H * u2 / (1.0 - H * u2);
-    g.bound = (float)(1.01 * (g1 + g2));
+// The filtering gate's scratch, laid out from `base` (nullptr: its size).
+size_t bind_filter(FilterArgs* f, char* base, long long T, long long H, long long E) {
+  size_t o = 0;
+  auto take = [&](size_t bytes) { char* at = base + o; o = align_up(o + bytes, 256); return at; };
+  FilterArgs g{};
+  g.wgt = reinterpret_cast<uint16_t*>(take(sizeof(uint16_t) * (size_t)(E * H)));
+  g.lt = reinterpret_cast<float*>(take(E > 128 ? sizeof(float) * (size_t)(T * E) : 0));
+  g.xn = reinterpret_cast<float*>(take(sizeof(float) * (size_t)T));
+  g.wn = reinterpret_cast<float*>(take(sizeof(float) * (size_t)E));
+  g.ch_g = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)(T * E)));
+  g.ch_e = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)(T * E)));
+  g.ch_l = reinterpret_cast<float*>(take(sizeof(float) * (size_t)(T * E)));
+  g.tok_base = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)T));
+  g.tok_n = reinterpret_cast<int32_t*>(take(sizeof(int32_t) * (size_t)T));
+  g.n_cands = reinterpret_cast<int32_t*>(take(sizeof(int32_t)));
+  if (f) {
+    const GateArgs a = *f;
+    *f = g;
+    static_cast<GateArgs&>(*f) = a;
   }
-  gate_prep_kernel<<<g.E, NTH, 0, s>>>(g);
-  if (g.E <= 32) gate_mfma_kernel<<<(g.T + 31) / 32, GATE_WAVES * WAVE, 0, s>>>(g);
-  // more experts: LDS-staged tiles, 128 tokens each when that still gives
-  // every CU a tile, else 64
-  else if (g.E <= 128) {
-    // logits and candidates without leaving LDS, 128 tokens per workgroup
-    // when that still gives every CU a tile, else 64
-    if (g.T >= 128 * 256) gate_tile2_kernel<128><<<(g.T + 127) / 128, 2 * NTH, 0, s>>>(g);
-    else gate_tile2_kernel<64><<<(g.T + 63) / 64, 2 * NTH, 0, s>>>(g);
-  } else {
-    // experts per lane of the candidate pass (16 lanes per token)
-    const int epl = g.E <= 64 ? 4 : g.E <= 128 ? 8 : 32;
-    const bool big = g.T >= 128 * 256;
-    const dim3 grid(big ? (g.T + 127) / 128 : (g.T + 63) / 64);
-    if (big) {
-      if (epl == 4) gate_tile_kernel<128, 4><<<grid, NTH, 0, s>>>(g);
-      else if (epl == 8) gate_tile_kernel<128, 8><<<grid, NTH, 0, s>>>(g);
-      else gate_tile_kernel<128, 32><<<grid, NTH, 0, s>>>(g);
-    } else {
-      if (epl == 4) gate_tile_kernel<64, 4><<<grid, NTH, 0, s>>>(g);
-      else if (epl == 8) gate_tile_kernel<64, 8><<<grid, NTH, 0, s>>>(g);
-      else gate_tile_kernel<64, 32><<<grid, NTH, 0, s>>>(g);
-    }
-  }
-  if (g.E <= 128 && g.k >= 4 && (long long)g.T * g.k >= 32768) {
-    // persistent over ranges of chains, at most T * E of them (with fewer
-    // chains than about 64 ranges, one chain per lane over many small
-    // workgroups spreads them over more CUs); a range holds at most
-    // 512 / k + 2 tokens, whose x rows a stage holds
-    const long long ranges = ((long long)g.T * g.E + GATE_CHAIN_STAGED_W - 1) / GATE_CHAIN_STAGED_W;
-    // two workgroups per CU (the kernel's registers and LDS allow it)
-    const int grid = (int)std::min<long long>(ranges, 512);
-    if (g.k >= 8) gate_chain_staged_kernel<72, 3><<<grid, GATE_CHAIN_STAGED_W, 0, s>>>(g);
-    else gate_chain_staged_kernel<136, 2><<<grid, GATE_CHAIN_STAGED_W, 0, s>>>(g);
-  } else {
-    gate_chain_kernel<<<std::min(16384, std::max(1, (g.T * g.k * 3 / 2 + WAVE - 1) / WAVE)), WAVE, 0, s>>>(g);
-  }
-  {
-    const dim3 grid((g.T + NTH - 1) / NTH);
-    const TableArgs t = tab ? *tab : TableArgs{};
-    auto final_ = [&](auto epl) {
-      constexpr int EPL = decltype(epl)::value;
-      if (tab) gate_final_kernel<EPL, true><<<grid, NTH, 0, s>>>(g, t);
-      else gate_final_kernel<EPL, false><<<grid, NTH, 0, s>>>(g, t);
-    };
-    if (g.E <= 16) final_(std::integral_constant<int, 1>{});
-    else if (g.E <= 32) final_(std::integral_constant<int, 2>{});
-    else if (g.E <= 64) final_(std::integral_constant<int, 4>{});
-    else if (g.E <= 128) final_(std::integral_constant<int, 8>{});
-    else final_(std::integral_constant<int, 32>{});
-  }
-  HIP_TRY(hipGetLastError());
-  return MOE_OK;
+  return o;
 }
 
 }  // namespace
@@ -153,6 +78,10 @@ struct moe_handle {
   moe_config cfg;
   int N = 0;
   int T = 0, xmax = 0, mt_max = 0, ctl_words = 0, nblk = 0, nseg = 0, nt0 = 0, nt1 = 0, nsplit = 1;
+  int nblk_cap = 0;  // count blocks the workspace holds (the gate's or tab_count_kernel's)
+  GateGeometry gate{};
+  bool filter = false;  // the gate filters (gate_filtered)
+  size_t off_gate = 0;  // the filtering gate's scratch, or the padded gate
   size_t arows = 0, orows = 0;  // row capacities of A and of Hbuf / O (the padded row map)
   int qx = 0, qxs = 0;
   moe_calib calib{};
@@ -160,7 +89,6 @@ struct moe_handle {
   moe_ws_layout lay{};
   size_t off_calib = 0, off_blk_cnt = 0, off_blk_off = 0, off_blk_bad = 0, off_rbnd = 0, off_uacc = 0, off_done = 0, off_ctl[2] = {0, 0};
   size_t off_part = 0;
-  size_t off_gate = 0;  // the gate's scratch (gate_layout)
   size_t off_sched = 0;  // schedule images, one per K option, and the stored plan (the table builder's)
   uint32_t calib_gen = 1;  // bumped by every moe_set_calib (a stored plan of an older table is stale)
   char* ws = nullptr;
@@ -315,11 +243,12 @@ void compute_layout(moe_handle* h) {
   L.plan = take(sizeof(moe_plan));
   L.err = take(sizeof(int32_t) * 4);
   h->off_calib = take(sizeof(DevCalib));
-  h->off_gate = take(gate_layout(T, c.hidden, c.n_experts).total);
+  h->off_gate = take(h->filter ? bind_filter(nullptr, nullptr, T, c.hidden, c.n_experts)
+                     : c.n_experts % 4 ? sizeof(uint16_t) * (size_t)gate_ldw(c.n_experts) * c.hidden : 0);
   h->off_sched = take(sizeof(int32_t) * (size_t)KOPT * SCHED_WORDS + sizeof(StoredPlan));
-  h->off_blk_cnt = take(sizeof(int32_t) * (size_t)h->nblk * El);
-  h->off_blk_off = take(sizeof(int32_t) * (size_t)h->nblk * El);
-  h->off_blk_bad = take(sizeof(int32_t) * (size_t)h->nblk);
+  h->off_blk_cnt = take(sizeof(int32_t) * (size_t)h->nblk_cap * El);
+  h->off_blk_off = take(sizeof(int32_t) * (size_t)h->nblk_cap * El);
+  h->off_blk_bad = take(sizeof(int32_t) * (size_t)h->nblk_cap);
   h->off_rbnd = take(sizeof(int32_t) * (size_t)El * (R + 1));
   h->off_uacc = take(sizeof(int32_t) * (size_t)R);
   h->off_done = take(sizeof(int32_t));
@@ -351,6 +280,13 @@ void move_units(const moe_handle* h, int* dt, int* ct) {
   const int per = h->T / (h->N * (FNTH / WAVE));
   *dt = per < 1 ? 1 : (per > DT ? DT : per);
   *ct = per < 1 ? 1 : (per > CT ? CT : per);
+}
+
+// The gate takes the tables' counting step along (one count block per
+// workgroup) unless one workgroup builds the tables, or its blocks are so
+// small that the table blocks could not sum their counts themselves.
+bool gate_counts(const moe_handle* h) {
+  return h->T > TAB_ONE_T && (long long)h->gate.grid * h->cfg.n_local_experts <= TAB_SUM_MAX && h->gate.tt <= TAB_TB;
 }
 
 TableArgs table_args(moe_handle* h, const int32_t* topk_idx) {
@@ -477,11 +413,11 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
 }  // namespace
 
 // ---- routing that allocates nothing ------------------------------------------
-// The gate's scratch for moe_route_topk_static lives in this file-scope
-// device array, so that the entry point needs no allocation.  Each GPU holds
-// its own copy until the process ends.  Host code must not use the array's
-// name as an address (it is a host-side stand-in): its device address is
-// looked up once per device with that device current and kept in
+// The gate's scratch for moe_route_topk_static (the filter's, or the padded
+// gate) lives in this file-scope device array, so that the entry point needs no allocation.  Each
+// GPU holds its own copy until the process ends.  Host code must not use the
+// array's name as an address (it is a host-side stand-in): its device address
+// is looked up once per device with that device current and kept in
 // g_scratch_ptr, which is what the kernels receive.
 static __device__ __align__(256) unsigned char scratch[MOE_ROUTE_STATIC_SCRATCH_BYTES];
 
@@ -534,6 +470,10 @@ moe_status moe_init(const moe_config* cfg, const moe_calib* calib, moe_handle** 
   h->nseg = cfg->n_local_experts + cfg->n_shared_experts;
   h->mt_max = (h->xmax + cfg->n_shared_experts * cfg->tokens_per_rank) / BM + MAX_K * h->nseg + 1;
   h->nblk = (h->T + NTH - 1) / NTH;
+  h->filter = gate_filtered(h->T, cfg->hidden, cfg->n_experts, cfg->top_k);
+  h->gate = gate_geometry(h->T, cfg->n_experts);
+  if (h->filter) h->gate = GateGeometry{0, 0, 0, NTH, h->nblk};  // gate_final's count blocks
+  h->nblk_cap = std::max(h->nblk, gate_counts(h) ? h->gate.grid : 0);
   h->nt0 = (2 * cfg->ffn + BN - 1) / BN;
   h->nt1 = (cfg->hidden + BN - 1) / BN;
   // split GEMM1 (K = F) when F is large against H, so its tiles are about as
@@ -684,6 +624,10 @@ moe_status moe_pack_weights(moe_handle* h, const uint16_t* w1, const uint16_t* w
 // (the routing's last kernel did it on the ids it chose).
 static moe_status launch_tables(moe_handle* h, const int32_t* topk_idx, hipStream_t s, bool counted) {
   TableArgs a = table_args(h, topk_idx);
+  if (counted) {
+    a.cb = h->gate.tt;
+    a.nblk = h->gate.grid;
+  }
   if (h->T <= TAB_TB) {
     tab_build_kernel<TAB_TB, true><<<1, TAB_TB + WAVE, 0, s>>>(a);
   } else if (h->T <= TAB_ONE_T) {
@@ -713,7 +657,7 @@ moe_status moe_route(moe_handle* h, const uint16_t* x, const uint16_t* wg, const
   if (!x || !wg || !topk_idx || !topk_w) return fail(MOE_ERR_INVALID_ARG, "NULL argument");
   if (top_k != h->cfg.top_k) return fail(MOE_ERR_INVALID_ARG, "top_k %d differs from the configured %d", top_k, h->cfg.top_k);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  GateArgs g{};
+  FilterArgs g{};
   g.x = x;
   g.wg = wg;
   g.bias = logit_bias;
@@ -723,12 +667,24 @@ moe_status moe_route(moe_handle* h, const uint16_t* x, const uint16_t* wg, const
   g.H = h->cfg.hidden;
   g.E = h->cfg.n_experts;
   g.k = top_k;
-  // the chain counter goes to the layer's stats (word ST_CANDS, reported)
-  bind_gate(g, h->ws + h->off_gate, gate_layout(g.T, g.H, g.E), at<int32_t>(h, h->lay.stats));
-  const TableArgs ta = table_args(h, topk_idx);
-  st = launch_gate(g, s, h->T > TAB_ONE_T ? &ta : nullptr);
-  if (st != MOE_OK) return st;
-  return launch_tables(h, topk_idx, s, true);
+  if (h->filter) bind_filter(&g, h->ws + h->off_gate, g.T, g.H, g.E);
+  g.cands = at<int32_t>(h, h->lay.stats) + ST_CANDS;
+  g.e0 = h->cfg.first_local_expert;
+  g.El = h->cfg.n_local_experts;
+  const bool count = gate_counts(h);
+  if (count) {
+    g.blk_cnt = at<int32_t>(h, h->off_blk_cnt);
+    g.blk_bad = at<int32_t>(h, h->off_blk_bad);
+    g.err = at<int32_t>(h, h->lay.err);
+  }
+  if (h->filter) {
+    g.n_cands = g.cands;  // reported
+    launch_gate_filter(g, s);
+  } else {
+    launch_gate(g, h->gate, at<uint16_t>(h, h->off_gate), s);
+  }
+  HIP_TRY(hipGetLastError());
+  return launch_tables(h, topk_idx, s, count);
 }
 
 moe_status moe_set_trace(moe_handle* h, void* buf, int64_t bytes) {
@@ -917,14 +873,11 @@ moe_status moe_route_topk_static(int32_t T, int32_t H, int32_t E, int32_t top_k,
   if (E < 1 || E > MAX_E) return fail(MOE_ERR_INVALID_ARG, "E must be in [1, %d]", MAX_E);
   if (top_k < 1 || top_k > MAX_TOPK || top_k > E)
     return fail(MOE_ERR_INVALID_ARG, "top_k must be in [1, min(E, %d)]", MAX_TOPK);
-  const GateLayout L = gate_layout(T, H, E);
-  if (L.total > (size_t)MOE_ROUTE_STATIC_SCRATCH_BYTES)
-    return fail(MOE_ERR_UNSUPPORTED, "T = %d, H = %d, E = %d needs %zu bytes of gate scratch, more than the %zu of "
-                "the static scratch (use moe_route)", T, H, E, L.total, (size_t)MOE_ROUTE_STATIC_SCRATCH_BYTES);
-  char* base = nullptr;
-  moe_status st = static_scratch(&base);
-  if (st != MOE_OK) return st;
-  GateArgs g{};
+  const size_t need = static_route_bytes(T, H, E);
+  if (need > (size_t)MOE_ROUTE_STATIC_SCRATCH_BYTES)
+    return fail(MOE_ERR_UNSUPPORTED, "T = %d, H = %d, E = %d counts %zu bytes, more than the %zu of the static "
+                "route's limit (use moe_route)", T, H, E, need, (size_t)MOE_ROUTE_STATIC_SCRATCH_BYTES);
+  FilterArgs g{};
   g.x = x;
   g.wg = wg;
   g.bias = logit_bias;
@@ -934,11 +887,21 @@ moe_status moe_route_topk_static(int32_t T, int32_t H, int32_t E, int32_t top_k,
   g.H = H;
   g.E = E;
   g.k = top_k;
-  // the chain counter (the one word that must start at zero) is cleared by
-  // the first kernel of the gate; every other region is written before it
-  // is read
-  bind_gate(g, base, L, reinterpret_cast<int32_t*>(base + L.stats));
-  return launch_gate(g, reinterpret_cast<hipStream_t>(stream), nullptr);
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  char* base = nullptr;
+  const bool filter = gate_filtered(T, H, E, top_k);
+  if (filter || E % 4) {
+    moe_status st = static_scratch(&base);
+    if (st != MOE_OK) return st;
+  }
+  if (filter) {
+    bind_filter(&g, base, T, H, E);
+    launch_gate_filter(g, s);
+  } else {
+    launch_gate(g, gate_geometry(T, E), reinterpret_cast<uint16_t*>(base), s);
+  }
+  HIP_TRY(hipGetLastError());
+  return MOE_OK;
 }
 
 }  // extern "C"

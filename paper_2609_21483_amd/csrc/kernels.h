@@ -14,19 +14,43 @@ struct GateArgs {
   const float* bias;   // [E] or NULL
   int32_t* topk_idx;
   float* topk_w;
-  uint16_t* wgt;       // [E][H] bf16: Wg transposed (workspace)
-  float* lt;           // [T][E] approximate logits without bias (workspace)
-  float* xn;           // [T] ||x_g||_2 (workspace)
-  float* wn;           // [E] ||w_e||_2 (workspace)
-  int32_t* ch_g;       // [T * E] chain list: token of each chain (workspace)
+  int32_t* cands;      // stats word ST_CANDS, or NULL
+  int32_t* blk_cnt;    // [workgroups][El] the tables' counts of each workgroup's tokens, or NULL
+  int32_t* blk_bad;    // [workgroups] tokens without k valid ids
+  int32_t* err;        // device error word (with blk_cnt)
+  int T, H, E, k, e0, El;
+  int ldw;             // values per row of wg as the kernel reads it (gate_ldw)
+};
+
+// The filtering gate's arguments: the gate's, and its scratch.
+struct FilterArgs : GateArgs {
+  uint16_t* wgt;       // [E][H] bf16: Wg transposed
+  float* lt;           // [T][E] approximate logits without bias (E > 128)
+  float* xn;           // [T] ||x_g||_2 (E > 128)
+  float* wn;           // [E] ||w_e||_2
+  int32_t* ch_g;       // [T * E] chain list: token of each chain
   int32_t* ch_e;       // [T * E] expert of each chain
   float* ch_l;         // [T * E] defined logit of each chain
   int32_t* tok_base;   // [T] first chain of each token
   int32_t* tok_n;      // [T] chains of each token
-  int32_t* stats;
+  int32_t* n_cands;    // chains in all
   float bound;         // |L - L~| <= bound * ||x|| * ||w|| (plus rounding of the bias add)
-  int T, H, E, k;
 };
+constexpr int GATE_CHAIN_STAGED_W = 512;  // chains per workgroup of gate_chain_staged_kernel
+void launch_gate_filter(const FilterArgs& a, hipStream_t s);
+
+// Launch geometry of the gate (gate_geometry): expert class, matrix
+// instruction shape, token wavefronts and tokens per workgroup, workgroups.
+struct GateGeometry {
+  int ec, large, tw, tt, grid;
+};
+constexpr int GATE_SIMDS = 1024;  // SIMDs of gfx950
+GateGeometry gate_geometry(int T, int E);
+bool gate_filtered(long long T, long long H, int E, int k);  // the filtering gate is the faster one
+// pad: device memory for the padded gate, H * gate_ldw(E) values (unused when
+// E is a multiple of 4)
+void launch_gate(const GateArgs& a, const GateGeometry& g, uint16_t* pad, hipStream_t s);
+constexpr int gate_ldw(int E) { return (E + 3) / 4 * 4; }
 
 struct TableArgs {
   const int32_t* topk_idx;
@@ -282,23 +306,7 @@ __host__ __device__ inline void cm_volumes(const int32_t* stats, int H, int F, i
   }
 }
 
-constexpr int GATE_WAVES = 4;  // wavefronts per workgroup of gate_mfma_kernel (each sums a quarter of H)
-
 // ---- launch prototypes ---------------------------------------------------------
-__global__ void gate_prep_kernel(GateArgs a);
-__global__ void gate_mfma_kernel(GateArgs a);
-template <int GT_M, int EPL>
-__global__ void gate_tile_kernel(GateArgs a);  // E > 32; GT_M tokens per workgroup (64 or 128),
-                                               // EPL >= E / 16 experts per lane in the candidate pass
-__global__ void gate_chain_kernel(GateArgs a);
-template <int CX, int NP>
-__global__ void gate_chain_staged_kernel(GateArgs a);  // E <= 128, CX tokens per range, NP stages
-constexpr int GATE_CHAIN_STAGED_W = 512;               // chains per workgroup of gate_chain_staged_kernel
-template <int GT_M>
-__global__ void gate_tile2_kernel(GateArgs a);  // 32 < E <= 128; GT_M tokens per workgroup (64 or 128)
-template <int EPL, bool COUNT>
-__global__ void gate_final_kernel(GateArgs a, TableArgs t);  // EPL >= E / 16 experts per lane; COUNT: also
-                                                             // tab_count_kernel's step on the chosen ids
 __global__ void tab_count_kernel(TableArgs a);
 __global__ void tab_scan_kernel(TableArgs a);
 template <int TBN, bool ONE>

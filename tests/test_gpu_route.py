@@ -239,3 +239,68 @@ def test_build_tables_workgroup_edges(B, R, Tr, E, k, El, S):
             assert st[10 + ki] == int((-(-rows // bm)).sum()) * (nt0 + nt1), K
     finally:
         hd.close()
+
+
+# gate classes and launch shapes: (T, H, E, k, bias)
+GATES = [
+    (1, 64, 1, 1, False), (17, 64, 8, 8, True), (5, 192, 3, 2, True),       # one stage of h; padded rows
+    (4097, 128, 16, 4, False), (40000, 64, 7, 3, True),                     # 16 experts: small shape, large shape
+    (2049, 128, 32, 5, True), (20000, 64, 30, 4, False),                    # 32
+    (1025, 192, 33, 6, False), (9000, 64, 64, 8, True),                     # 64
+    (31, 320, 65, 8, True), (1030, 128, 128, 3, False), (5000, 64, 126, 8, True),  # 128
+    (300, 128, 129, 8, True), (1100, 64, 256, 1, False), (3000, 96 * 2, 200, 7, True),  # 256
+    (67, 128, 257, 4, False), (1500, 64, 512, 8, True),                     # 512
+    (32768, 64, 66, 2, True), (16384, 1536, 72, 4, False),                  # the filter, one and four entries per token
+    (32768, 4096, 130, 1, False),                                           # the filter above 128 experts
+]
+
+
+@pytest.mark.parametrize("T,H,E,k,bias", GATES)
+def test_gate_classes(B, T, H, E, k, bias):
+    """Every expert class and launch shape of the gate, ragged token counts and
+    expert counts, a row of zeros and tied experts: ids bit for bit."""
+    rng = torch.Generator().manual_seed(T * 1000 + E)
+    x = torch.randn(T, H, generator=rng).to(torch.bfloat16)
+    wg = (0.05 * torch.randn(H, E, generator=rng)).to(torch.bfloat16)
+    x[T // 2] = 0
+    if E > 2:
+        wg[:, E - 1] = wg[:, 1]
+    b = torch.randn(E, generator=rng) if bias else None
+    from tests.cases import oracle_logits
+    lg = oracle_logits(W.as_u16_numpy(x), W.as_u16_numpy(wg), None if b is None else b.numpy())
+    idx_ref, w_ref = O.softmax_topk(lg, k)
+    idx = torch.full((T, k), -7, dtype=torch.int32, device="cuda")
+    w = torch.zeros((T, k), dtype=torch.float32, device="cuda")
+    B.moe_route_topk_static(T, H, E, k, x.cuda(), wg.cuda(), None if b is None else b.cuda(), idx, w)
+    torch.cuda.synchronize()
+    assert np.array_equal(idx.cpu().numpy(), idx_ref)
+    assert np.max(np.abs(w.cpu().numpy() - w_ref)) <= 1e-6
+
+
+def test_gate_masked_experts(B):
+    """A bias of -inf or of the lowest float takes an expert out unless too few
+    are left, when the masked ones follow by id with weight 0; a NaN logit is
+    never chosen."""
+    T, H, E, k = 40, 128, 12, 4
+    rng = torch.Generator().manual_seed(5)
+    x = torch.randn(T, H, generator=rng).to(torch.bfloat16)
+    wg = (0.05 * torch.randn(H, E, generator=rng)).to(torch.bfloat16)
+    for keep, low in ((6, float("-inf")), (6, torch.finfo(torch.float32).min), (2, float("-inf"))):
+        b = torch.zeros(E)
+        b[keep:] = low
+        lg = O.gate_logits(W.as_u16_numpy(x), W.as_u16_numpy(wg), b.numpy())
+        order = np.argsort(-lg.astype(np.float64), axis=1, kind="stable")[:, :k]
+        idx = torch.full((T, k), -7, dtype=torch.int32, device="cuda")
+        w = torch.zeros((T, k), dtype=torch.float32, device="cuda")
+        B.moe_route_topk_static(T, H, E, k, x.cuda(), wg.cuda(), b.cuda(), idx, w)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy(), order), (keep, low)
+        wn = w.cpu().numpy()
+        assert np.all(wn[:, keep:] == 0) and np.allclose(wn.sum(axis=1), 1, atol=1e-6)
+    b = torch.zeros(E)
+    b[3] = float("nan")
+    idx = torch.full((T, k), -7, dtype=torch.int32, device="cuda")
+    B.moe_route_topk_static(T, H, E, k, x.cuda(), wg.cuda(), b.cuda(), idx, torch.zeros((T, k), device="cuda"))
+    torch.cuda.synchronize()
+    got = idx.cpu().numpy()
+    assert not np.any(got == 3) and got.min() >= 0 and got.max() < E
