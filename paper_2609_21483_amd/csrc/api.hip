@@ -414,11 +414,11 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
 
 // ---- routing that allocates nothing ------------------------------------------
 // The gate's scratch for moe_route_topk_static (the filter's, or the padded
-// gate) lives in this file-scope device array, so that the entry point needs no allocation.  Each
-// GPU holds its own copy until the process ends.  Host code must not use the
-// array's name as an address (it is a host-side stand-in): its device address
-// is looked up once per device with that device current and kept in
-// g_scratch_ptr, which is what the kernels receive.
+// gate) lives in this file-scope device array, so that the entry point needs
+// no allocation.  Each GPU holds its own copy until the process ends.  Host
+// code must not use the array's name as an address (it is a host-side
+// stand-in): its device address is looked up once per device with that device
+// current and kept in g_scratch_ptr, which is what the kernels receive.
 static __device__ __align__(256) unsigned char scratch[MOE_ROUTE_STATIC_SCRATCH_BYTES];
 
 namespace {
@@ -875,8 +875,8 @@ moe_status moe_route_topk_static(int32_t T, int32_t H, int32_t E, int32_t top_k,
     return fail(MOE_ERR_INVALID_ARG, "top_k must be in [1, min(E, %d)]", MAX_TOPK);
   const size_t need = static_route_bytes(T, H, E);
   if (need > (size_t)MOE_ROUTE_STATIC_SCRATCH_BYTES)
-    return fail(MOE_ERR_UNSUPPORTED, "T = %d, H = %d, E = %d counts %zu bytes, more than the %zu of the static "
-                "route's limit (use moe_route)", T, H, E, need, (size_t)MOE_ROUTE_STATIC_SCRATCH_BYTES);
+    return fail(MOE_ERR_UNSUPPORTED, "T = %d, H = %d, E = %d counts %zu bytes of gate scratch, more than the "
+                "%zu of the static scratch (use moe_route)", T, H, E, need, (size_t)MOE_ROUTE_STATIC_SCRATCH_BYTES);
   FilterArgs g{};
   g.x = x;
   g.wg = wg;
