@@ -380,7 +380,9 @@ moe_status moe_plan_host(const moe_handle* h, double w_comp, double w_dispatch,
 
 /* Tile geometry of the grouped GEMM for this shape: rows per tile (bm), GEMM0
  * tiles per row tile (nt0: column tiles over 2F) and GEMM1 tiles per row tile
- * (nt1: column tiles over H times the split-K factor of GEMM1). */
+ * (nt1: column tiles over H times the split-K factor of GEMM1), in whole slabs
+ * of 256 columns, as the cost model counts them (layers of few rows may run
+ * narrower tiles). */
 moe_status moe_tile_geometry(const moe_handle* h, int32_t* bm, int32_t* nt0, int32_t* nt1);
 
 #ifdef __cplusplus

@@ -78,6 +78,7 @@ struct moe_handle {
   moe_config cfg;
   int N = 0;
   int T = 0, xmax = 0, mt_max = 0, ctl_words = 0, nblk = 0, nseg = 0, nt0 = 0, nt1 = 0, nsplit = 1;
+  int few = 0;  // few rows per expert (few_rows)
   int nblk_cap = 0;  // count blocks the workspace holds (the gate's or tab_count_kernel's)
   GateGeometry gate{};
   bool filter = false;  // the gate filters (gate_filtered)
@@ -102,7 +103,7 @@ struct moe_handle {
   long long* trace = nullptr;
   int trace_cap = 0, trace_rec0 = 0;
   bool resident_ok = false;  // the megakernel's N workgroups fit the GPU at once
-  bool stack_resident_ok = false;  // the same for the stacked megakernel
+  bool stack_resident_ok[2] = {false, false};  // the same for the stacked megakernels (one for layers of few rows)
 };
 
 namespace {
@@ -289,6 +290,21 @@ bool gate_counts(const moe_handle* h) {
   return h->T > TAB_ONE_T && (long long)h->gate.grid * h->cfg.n_local_experts <= TAB_SUM_MAX && h->gate.tt <= TAB_TB;
 }
 
+// A layer of few rows (decode steps): at most FEW_ROWS routed rows per expert
+// on average, 64 of rank 0's tokens in a shared expert, so that a row tile is
+// nearly always within a narrow tile's fast range.  Its time is that of
+// streaming the experts' weights; rows are gathered from x by GEMM0 itself
+// (with 32-bit byte offsets), so no tile waits for the dispatch, and a phase
+// with few tiles runs in narrow ones (routing and layer of 32 decode tokens of
+// the fine-grained shape 91 -> 84 us, 64 of the Mixtral shape 210 -> 199).
+// These layers have kernels of their own: with this code in the one kernel
+// the tiles of large layers ran 2% slower.
+int few_rows(const moe_config& c) {
+  const long long T = (long long)c.n_src_ranks * c.tokens_per_rank;
+  return T * c.top_k <= (long long)FEW_ROWS * c.n_experts && (c.n_shared_experts == 0 || c.tokens_per_rank <= 64) &&
+         T * c.hidden * 2 < (1LL << 32);
+}
+
 TableArgs table_args(moe_handle* h, const int32_t* topk_idx) {
   TableArgs a{};
   a.topk_idx = topk_idx;
@@ -321,8 +337,10 @@ TableArgs table_args(moe_handle* h, const int32_t* topk_idx) {
   a.cb = NTH;
   a.nblk = h->nblk;
   a.S = h->cfg.n_shared_experts;
-  a.nt0 = h->nt0;
-  a.g1 = h->nt1 * h->nsplit;
+  a.wide0 = h->nt0;
+  a.wide1 = h->nt1 * h->nsplit;
+  a.few = h->few;
+  a.nsplit = h->nsplit;
   move_units(h, &a.dt, &a.ct);
   a.H = h->cfg.hidden;
   a.F = h->cfg.ffn;
@@ -356,19 +374,17 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
   FwdArgs a{};
   a.T = h->T;
   a.Tr = c.tokens_per_rank;
-  a.R = c.n_src_ranks;
   a.H = c.hidden;
   a.F = c.ffn;
   a.k = c.top_k;
   a.El = c.n_local_experts;
   a.S = c.n_shared_experts;
   a.e0 = c.first_local_expert;
-  a.N = h->N;
   a.nt0 = h->nt0;
-  a.nt1 = h->nt1;
+  a.nt1 = h->few ? (h->cfg.hidden + THIN_N - 1) / THIN_N : h->nt1;
   a.nsplit = h->nsplit;
+  a.gather = h->few;
   move_units(h, &a.dt, &a.ct);
-  a.xmax = h->xmax;
   a.mt_max = h->mt_max;
   a.ctl_words = h->ctl_words;
   a.qx = h->qx;
@@ -380,6 +396,7 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
   a.w2t = a.w13 ? a.w13 + (size_t)h->nseg * slab_rows(2 * c.ffn) * c.hidden : nullptr;
   a.y = y;
   a.slot = at<int32_t>(h, h->lay.slot);
+  a.inv = at<int32_t>(h, h->lay.inv);
   a.sub_off = at<int32_t>(h, h->lay.sub_off);
   a.row_off = at<int32_t>(h, h->lay.row_off);
   a.sched = at<int32_t>(h, h->off_sched);
@@ -396,7 +413,9 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
   a.plan_out = at<moe_plan>(h, h->lay.plan);
   a.calib = at<DevCalib>(h, h->off_calib);
   a.mode = mode;
-  a.move_steal = mode == MOE_MODE_DYNAMIC ? 1 : 0;
+  // (rows gathered from x: nobody waits for the dispatch, the movement
+  // workers run it by themselves)
+  a.move_steal = mode == MOE_MODE_DYNAMIC && !a.gather ? 1 : 0;
   a.forced = forced ? 1 : 0;
   if (forced) a.fplan = *forced;
   a.timeout_ticks = h->timeout_ticks;
@@ -470,12 +489,12 @@ moe_status moe_init(const moe_config* cfg, const moe_calib* calib, moe_handle** 
   h->nseg = cfg->n_local_experts + cfg->n_shared_experts;
   h->mt_max = (h->xmax + cfg->n_shared_experts * cfg->tokens_per_rank) / BM + MAX_K * h->nseg + 1;
   h->nblk = (h->T + NTH - 1) / NTH;
+  h->nt0 = (2 * cfg->ffn + BN - 1) / BN;
+  h->nt1 = (cfg->hidden + BN - 1) / BN;
   h->filter = gate_filtered(h->T, cfg->hidden, cfg->n_experts, cfg->top_k);
   h->gate = gate_geometry(h->T, cfg->n_experts);
   if (h->filter) h->gate = GateGeometry{0, 0, 0, NTH, h->nblk};  // gate_final's count blocks
   h->nblk_cap = std::max(h->nblk, gate_counts(h) ? h->gate.grid : 0);
-  h->nt0 = (2 * cfg->ffn + BN - 1) / BN;
-  h->nt1 = (cfg->hidden + BN - 1) / BN;
   // split GEMM1 (K = F) when F is large against H, so its tiles are about as
   // long as GEMM0's (K = H) and there are enough of them to fill the CUs
   if (cfg->gemm1_split) {
@@ -484,9 +503,11 @@ moe_status moe_init(const moe_config* cfg, const moe_calib* calib, moe_handle** 
     h->nsplit = cfg->ffn >= 3 * cfg->hidden ? 4 : (2 * cfg->ffn >= 3 * cfg->hidden ? 2 : 1);
     while (h->nsplit > 1 && cfg->ffn % (32 * h->nsplit)) h->nsplit /= 2;
   }
+  h->few = few_rows(*cfg);
   // readiness counters per row tile (dispatched rows, GEMM0 columns, GEMM1
   // columns) and, when GEMM1 is split, split arrivals per (row, column) tile
-  h->ctl_words = CTL_READY + (3 * h->mt_max + (h->nsplit > 1 ? h->mt_max * h->nt1 : 0)) * CTL_PAD;
+  const int nt1 = h->few ? (cfg->hidden + THIN_N - 1) / THIN_N : h->nt1;
+  h->ctl_words = CTL_READY + (3 * h->mt_max + (h->nsplit > 1 ? h->mt_max * nt1 : 0)) * CTL_PAD;
   // per (stage, slab class) tile queue heads of the megakernel, then of the
   // serial GEMM kernels
   h->qx = h->ctl_words;
@@ -722,8 +743,8 @@ moe_status moe_forward(moe_handle* h, const uint16_t* x, const int32_t* topk_idx
   FwdArgs a = fwd_args(h, x, topk_idx, topk_w, packed, y, mode, forced);
   if (mode == MOE_MODE_SERIAL) {
     serial_dispatch_kernel<<<h->N, FNTH, 0, s>>>(a);
-    serial_gemm0_kernel<<<h->N, FNTH, 0, s>>>(a);
-    serial_gemm1_kernel<<<h->N, FNTH, 0, s>>>(a);
+    (h->few ? serial_gemm0_few_kernel : serial_gemm0_kernel)<<<h->N, FNTH, 0, s>>>(a);
+    (h->few ? serial_gemm1_few_kernel : serial_gemm1_kernel)<<<h->N, FNTH, 0, s>>>(a);
     serial_combine_kernel<<<h->N, FNTH, 0, s>>>(a);
     HIP_TRY(hipGetLastError());
   } else {
@@ -732,9 +753,10 @@ moe_status moe_forward(moe_handle* h, const uint16_t* x, const int32_t* topk_idx
     // ordinary launch: on an otherwise idle GPU one workgroup lands on each
     // CU; a cooperative launch would hold it until all earlier work on the
     // device has drained (~20 us a layer).
-    st = check_resident(h, reinterpret_cast<const void*>(&moe_megakernel), h->resident_ok);
+    const auto kernel = h->few ? moe_megakernel_few : moe_megakernel;
+    st = check_resident(h, reinterpret_cast<const void*>(kernel), h->resident_ok);
     if (st != MOE_OK) return st;
-    moe_megakernel<<<h->N, FNTH, 0, s>>>(a);
+    kernel<<<h->N, FNTH, 0, s>>>(a);
     HIP_TRY(hipGetLastError());
   }
   h->launch_seq++;
@@ -769,8 +791,10 @@ moe_status moe_forward_stack(moe_handle* const* layers, int32_t n_layers, const 
       return fail(MOE_ERR_STATE, "layer %d: routing tables were not built from its topk_idx", l);
     if (forced && (forced->c < 1 || forced->c >= N)) return fail(MOE_ERR_INVALID_ARG, "forced c must be in [1, N-1]");
   }
-  moe_status st = check_resident(layers[0], reinterpret_cast<const void*>(&moe_megakernel_stack),
-                                 layers[0]->stack_resident_ok);
+  bool few = false;
+  for (int l = 0; l < n_layers; ++l) few = few || layers[l]->few;
+  const auto kernel = few ? moe_megakernel_few_stack : moe_megakernel_stack;
+  moe_status st = check_resident(layers[0], reinterpret_cast<const void*>(kernel), layers[0]->stack_resident_ok[few]);
   if (st != MOE_OK) return st;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   StackArgs sa{};
@@ -784,7 +808,7 @@ moe_status moe_forward_stack(moe_handle* const* layers, int32_t n_layers, const 
     a.stack_next = l + 1 < n_layers ? 1 : 0;
     a.trace = nullptr;
   }
-  moe_megakernel_stack<<<N, FNTH, 0, s>>>(sa);
+  kernel<<<N, FNTH, 0, s>>>(sa);
   HIP_TRY(hipGetLastError());
   for (int l = 0; l < n_layers; ++l) layers[l]->launch_seq++;
   return MOE_OK;
@@ -812,8 +836,8 @@ moe_status moe_run_stages(moe_handle* h, const uint16_t* x, const int32_t* topk_
     z.T = 0;
     serial_dispatch_kernel<<<1, FNTH, 0, s>>>(z);
   }
-  if (stages & 2) serial_gemm0_kernel<<<n_workers, FNTH, 0, s>>>(a);
-  if (stages & 4) serial_gemm1_kernel<<<n_workers, FNTH, 0, s>>>(a);
+  if (stages & 2) (h->few ? serial_gemm0_few_kernel : serial_gemm0_kernel)<<<n_workers, FNTH, 0, s>>>(a);
+  if (stages & 4) (h->few ? serial_gemm1_few_kernel : serial_gemm1_kernel)<<<n_workers, FNTH, 0, s>>>(a);
   if (stages & 8) serial_combine_kernel<<<n_workers, FNTH, 0, s>>>(a);
   HIP_TRY(hipGetLastError());
   h->launch_seq++;

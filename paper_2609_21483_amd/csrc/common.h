@@ -17,18 +17,23 @@ constexpr int WAVE = 64;
 // grouped-GEMM tile: BM rows x BN columns (bf16 MFMA 32x32x16, see gemm.h)
 constexpr int BM = 256;
 constexpr int BN = 256;
+constexpr int THIN_N = 64;      // columns of a narrow tile
+constexpr int FEW_ROWS = 48;    // layers of few rows: at most this many per expert, on average
 constexpr int MAX_SPLIT = 8;    // split-K factor limit of GEMM1
 
 // Packed expert weights are slab-tiled GEMM B operands: an [R][K] matrix
-// (R output columns, K deep) is stored as ceil(R / 256) slabs of 256 rows;
-// slab j holds its K / 32 k-steps one after the other, each a block of 256
-// rows x 32 bf16 (row r of the block at r * 64 bytes).  Rows past R are zero.
+// (R output columns, K deep), padded with zero rows to whole 256-row slabs, is
+// stored as strips of 64 rows; a strip holds its K / 32 k-steps one after the
+// other, each a block of 64 rows x 32 bf16 (row r of the block at r * 64
+// bytes).  A tile of 64 columns streams one strip front to back, one of 256
+// columns four of them.
 constexpr int SLAB = 256;
+constexpr int STRIP = 64;
 constexpr int SLAB_K = 32;
 __host__ __device__ inline long long slab_rows(long long R) { return (R + SLAB - 1) / SLAB * SLAB; }
 // element offset of (row n, column k) in a slab-tiled [R][K] matrix
 __host__ __device__ inline long long slab_index(long long n, long long k, long long K) {
-  return ((n / SLAB) * (K / SLAB_K) + k / SLAB_K) * (SLAB * SLAB_K) + (n % SLAB) * SLAB_K + k % SLAB_K;
+  return ((n / STRIP) * (K / SLAB_K) + k / SLAB_K) * (STRIP * SLAB_K) + (n % STRIP) * SLAB_K + k % SLAB_K;
 }
 
 constexpr int DT = 8;           // most tokens per dispatch unit (one wavefront; DT * top_k <= 64)

@@ -40,7 +40,11 @@ struct Scratch {
 };
 
 // slabs of a phase (see class_slabs)
-__device__ __forceinline__ int phase_slabs(const FwdArgs& a, int ph) { return ph == 0 ? a.nt0 : a.nt1 * a.nsplit; }
+template <bool FEW>
+__device__ __forceinline__ int phase_slabs(const FwdArgs& a, const Sched& S, int ph) {
+  if (FEW) return ph == 0 ? S.nt[0] : S.nt[1] * a.nsplit;
+  return ph == 0 ? a.nt0 : a.nt1 * a.nsplit;
+}
 
 // A launch's schedule for chunk count K: the stored image (struct Sched,
 // built with the routing tables) copied into S after the plan fields, which
@@ -483,7 +487,7 @@ __device__ __forceinline__ bool combine_tokens(const FwdArgs& a, const Sched* S,
   }
   if (S) {
     // every column tile of the row tile (split ones reduced)
-    if (!wave_wait_all(a, id >= 0 ? &a.ctl[CTL_READY + (2 * a.mt_max + id) * CTL_PAD] : nullptr, a.nt1)) return false;
+    if (!wave_wait_all(a, id >= 0 ? &a.ctl[CTL_READY + (2 * a.mt_max + id) * CTL_PAD] : nullptr, S->nt[1])) return false;
     if (a.trace) t_ready = now_ticks();
   }
   __builtin_amdgcn_wave_barrier();
@@ -513,6 +517,7 @@ struct TileRef {
 // queue holds its stage's tiles by readiness level, then segment, then slab,
 // then row tile: the first claims go to the row tiles whose inputs are
 // complete first, and the tiles of one level share their weight slabs.
+template <bool FEW>
 __device__ __forceinline__ TileRef decode_tile(const FwdArgs& a, const Sched& S, int code) {
   const int stage = code >> 24, x = (code >> 21) & (NXCD - 1);
   int i = code & ((1 << 21) - 1);
@@ -520,22 +525,21 @@ __device__ __forceinline__ TileRef decode_tile(const FwdArgs& a, const Sched& S,
   const int qp = stage_qph(stage, S.K);
   r.q = qp >> 1;
   r.ph = qp & 1;
-  const int nsx = class_slabs(phase_slabs(a, r.ph), x);
+  const int nsx = class_slabs(phase_slabs<FEW>(a, S, r.ph), x);
   const int* cum = S.lvl[r.q];
   int L = 0;
   while (L < NLVL && i >= nsx * cum[L]) ++L;
   if (L > 0) i -= nsx * cum[L - 1];
-  int seg = 0, rows = 0, c = 1, lo = 0;
-  for (; seg < S.nseg; ++seg) {
-    rows = S.rows[r.q * S.nseg + seg];
-    const bool sh = seg >= a.El;
-    c = level_tiles(rows, sh, L);
-    if (i < nsx * c) {
-      lo = level_lo(rows, sh, L);
-      break;
-    }
-    i -= nsx * c;
-  }
+  // the segment: the last of the level's (shared experts at level 0, local
+  // experts at level 1) whose first tile of the class is at or before i, one
+  // segment per lane (walking them took 50 ns a segment on every tile)
+  static_assert(NLVL == 1 && MAX_EL <= WAVE && MAX_S <= WAVE, "one lane per segment of a level");
+  const int s0 = r.q * S.nseg + (L == 0 ? a.El : 0), ns = L == 0 ? a.S : a.El;
+  const int lane = gemm::lane_here();
+  const int at = lane < ns ? nsx * (S.mb[s0 + lane] - S.mb[s0]) : 1 << 30;
+  const int sl = __builtin_popcountll(__builtin_amdgcn_ballot_w64(at <= i)) - 1;
+  i -= __builtin_amdgcn_readlane(at, sl);
+  const int seg = (L == 0 ? a.El : 0) + sl, rows = S.rows[s0 + sl], c = (rows + BM - 1) / BM, lo = 0;
   r.seg = seg;
   r.mt = lo + i % c;
   const int slab = x + NXCD * (i / c);
@@ -575,12 +579,50 @@ __device__ __forceinline__ int claim_tile(const FwdArgs& a, const Sched& S, int 
   return -1;
 }
 
+// A narrow tile (gemm::mainloop_thin).  GEMM0 takes routed rows straight from
+// x (row r of the tile is token inv[slot] / k).
+// Returns false when the launch was aborted.
+template <int CP, typename ReadyFn, typename ClaimFn>
+__device__ __forceinline__ bool run_gemm_thin(const FwdArgs& a, const Sched& S, const TileRef& r, char* ring,
+                                              ReadyFn&& ready, ClaimFn&& claim_next, int& nxt) {
+  const int qs = r.q * S.nseg + r.seg;
+  const size_t orow = (size_t)S.row0[qs] + (size_t)r.mt * BM;
+  const int n0 = r.nt * THIN_N;  // first column: a strip of the weights
+  gemm::AccThin acc;
+#pragma unroll
+  for (int nb = 0; nb < gemm::NB; ++nb) acc[nb] = f32x16_t{};
+  gemm::AThin A;
+  const uint16_t* B;
+  int Kd;
+  if (r.ph == 0) {
+    const int first = S.sbase[qs] + r.mt * BM;  // slot (routed) or token (shared) of the tile's first row
+    A = {reinterpret_cast<const char*>(a.x), 0, a.H * 2, first, a.k, r.seg < a.El ? a.inv + first : nullptr, r.rows};
+    B = a.w13 + (size_t)r.seg * slab_rows(2 * a.F) * a.H + (size_t)n0 * a.H;
+    Kd = a.H;
+  } else {
+    Kd = a.F / a.nsplit;
+    A = {reinterpret_cast<const char*>(a.Hb + (orow >> 5) * (size_t)a.F * gemm::GROUP + (size_t)r.ks * Kd * gemm::GROUP),
+         a.F * gemm::GROUP * 2, 0, 0, 1, nullptr, r.rows};
+    B = a.w2t + (size_t)r.seg * slab_rows(a.H) * a.F + (size_t)n0 * a.F + (size_t)r.ks * Kd * STRIP;
+  }
+  if (!gemm::mainloop_thin(acc, A, B, Kd, ring, ready)) return false;
+  if (threadIdx.x == 0) nxt = claim_next();
+  if (r.ph == 0)
+    gemm::store_silu_thin<CP>(acc, a.Hb + (orow >> 5) * (size_t)a.F * gemm::GROUP + (size_t)(n0 / 2) * gemm::GROUP,
+                              a.F * gemm::GROUP, r.rows, ring);
+  else if (a.nsplit == 1)
+    gemm::store_bf16_thin<CP>(acc, a.O + orow * a.H + n0, a.H, r.rows, ring);
+  else
+    gemm::store_f32_thin<CP>(acc, a.part + ((size_t)r.ks * a.prow + orow) * a.H + n0, a.H, r.rows);
+  return true;
+}
+
 // Runs one GEMM0 tile or one split of a GEMM1 tile.  One mainloop instance
 // serves both GEMMs; only the operands and the epilogue differ.
 // Thread 0 claims the next tile (claim_next) between the mainloop and the
 // epilogue (returned on thread 0), so the claim's round trip overlaps the
 // epilogue stores.
-template <int CP, typename ClaimFn>
+template <bool FEW, int CP, typename ClaimFn>
 __device__ __forceinline__ int run_gemm(const FwdArgs& a, const Sched& S, const TileRef& r, char* ring,
                                         ClaimFn&& claim_next) {
   const int qs = r.q * S.nseg + r.seg;
@@ -596,23 +638,25 @@ __device__ __forceinline__ int run_gemm(const FwdArgs& a, const Sched& S, const 
   A.rows = r.rows;
   if (r.ph == 0) {
     const size_t arow = (size_t)S.arow0[qs] + (size_t)r.mt * BM;
-    if (r.seg < a.El) {
-      A = {a.A + (arow >> 5) * (size_t)a.H * gemm::GROUP, a.H, (int)(arow & 31), a.H * gemm::GROUP * 2, r.rows};
+    if (r.seg >= a.El) {
+      A = {a.x + arow * a.H, a.H, 0, 0, r.rows, nullptr, 1};
+    } else if (FEW && a.gather) {
+      A = {a.x, a.H, 0, 0, r.rows, a.inv + S.sbase[qs] + r.mt * BM, a.k};
     } else {
-      A = {a.x + arow * a.H, a.H, 0, 0, r.rows};
+      A = {a.A + (arow >> 5) * (size_t)a.H * gemm::GROUP, a.H, (int)(arow & 31), a.H * gemm::GROUP * 2, r.rows, nullptr, 1};
     }
     Bop = a.w13 + (size_t)r.seg * slab_rows(2 * a.F) * a.H + (size_t)n0 * a.H;
     Kd = a.H;
   } else {
     const int kl = a.F / a.nsplit;
     A = {a.Hb + (orow >> 5) * (size_t)a.F * gemm::GROUP + (size_t)r.ks * kl * gemm::GROUP, a.F, (int)(orow & 31),
-         a.F * gemm::GROUP * 2, r.rows};
-    Bop = a.w2t + (size_t)r.seg * slab_rows(a.H) * a.F + (size_t)n0 * a.F + (size_t)r.ks * kl * SLAB;
+         a.F * gemm::GROUP * 2, r.rows, nullptr, 1};
+    Bop = a.w2t + (size_t)r.seg * slab_rows(a.H) * a.F + (size_t)n0 * a.F + (size_t)r.ks * kl * STRIP;
     Kd = kl;
   }
   gemm::Acc acc;
   gemm::zero(acc);
-  gemm::mainloop(acc, A, Bop, Kd, ring);
+  gemm::mainloop(acc, A, Bop, r.ph == 0 ? a.H : a.F, Kd, ring);
   int nxt = -1;
   if (threadIdx.x == 0) nxt = claim_next();
   if (r.ph == 0) {
@@ -684,7 +728,7 @@ __device__ __forceinline__ void reduce_split(const FwdArgs& a, size_t orow, int 
 // After a GEMM1 item's partial stores have completed (all threads, past a
 // barrier): counts its arrival; the last split of the tile reduces it.
 // Returns true on the workgroup that reduced (its O stores still draining).
-template <int CP>
+template <bool FEW, int CP>
 __device__ __forceinline__ bool arrive_and_reduce(const FwdArgs& a, const Sched& S, Scratch& W, const TileRef& r,
                                                   int id) {
   if (threadIdx.x == 0)
@@ -694,7 +738,8 @@ __device__ __forceinline__ bool arrive_and_reduce(const FwdArgs& a, const Sched&
   __syncthreads();
   if (!last) return false;
   const size_t orow = (size_t)S.row0[r.q * S.nseg + r.seg] + (size_t)r.mt * BM;
-  reduce_split<CP>(a, orow, r.rows, r.nt * BN, min(BN, a.H - r.nt * BN));
+  const int bn = FEW ? S.bn[1] : BN;
+  reduce_split<CP>(a, orow, r.rows, r.nt * bn, min(bn, a.H - r.nt * bn));
   return true;
 }
 
@@ -742,7 +787,7 @@ __device__ __forceinline__ void prologue_plan(const FwdArgs& a, Sched& S, Scratc
   moe_plan p;
   // the plan the routing's last kernel evaluated on these tables, when the
   // calibration has not changed since (W.bc[6]); else evaluated here
-  if (model && !W.bc[6] && tid < WAVE) model_plan(W.cal, W.st, a.H, a.F, a.S * a.Tr, a.N, p);
+  if (model && !W.bc[6] && tid < WAVE) model_plan(W.cal, W.st, a.H, a.F, a.S * a.Tr, (int)gridDim.x, p);
   if (tid == 0) {
     if (model && W.bc[6]) {
       p = sp.p;
@@ -842,6 +887,7 @@ __device__ __forceinline__ bool wait_rows(const FwdArgs& a, const Sched& S, Scra
 // tile), runs, and is published once every thread's agent-coherent output
 // stores have completed, with one relaxed increment.  The next tile is claimed
 // between mainloop and epilogue.  Returns false when the launch was aborted.
+template <bool FEW>
 __device__ __forceinline__ bool compute_tiles(const FwdArgs& a, const Sched& S, Scratch& W, char* ring, int ticket,
                                               int max_tiles) {
   if (max_tiles <= 0) return true;
@@ -855,16 +901,28 @@ __device__ __forceinline__ bool compute_tiles(const FwdArgs& a, const Sched& S, 
   for (int done = 1; t >= 0; ++done) {
     jitter(a, 0x40000u + (uint32_t)t);
     const uint64_t t0 = a.trace ? now_ticks() : 0;
-    const TileRef r = decode_tile(a, S, t);
+    const TileRef r = decode_tile<FEW>(a, S, t);
     const int id = S.mb[r.q * S.nseg + r.seg] + r.mt;
-    if (r.ph == 0) {
-      if (r.seg < a.El && !wait_rows(a, S, W, &a.ctl[CTL_READY + id * CTL_PAD], r.rows)) return false;
-    } else {
-      if (!wait_geq(a, W, &a.ctl[CTL_READY + (a.mt_max + id) * CTL_PAD], a.nt0)) return false;
-    }
-    const uint64_t t1 = a.trace ? now_ticks() : 0;
+    uint64_t t1 = 0;
+    auto ready = [&] {
+      bool ok = true;
+      if (r.ph == 0) {
+        if (r.seg < a.El && !(FEW && a.gather)) ok = wait_rows(a, S, W, &a.ctl[CTL_READY + id * CTL_PAD], r.rows);
+      } else {
+        ok = wait_geq(a, W, &a.ctl[CTL_READY + (a.mt_max + id) * CTL_PAD], FEW ? S.nt[0] : a.nt0);
+      }
+      if (a.trace) t1 = now_ticks();
+      return ok;
+    };
     const bool more = done < max_tiles;
-    const int nxt = run_gemm<gemm::CP_SC1>(a, S, r, ring, [&] { return more ? claim_tile(a, S, a.qx, -1, home, stage, exhausted) : -1; });
+    auto next = [&] { return more ? claim_tile(a, S, a.qx, -1, home, stage, exhausted) : -1; };
+    int nxt = -1;
+    if (FEW && S.bn[r.ph] != BN) {
+      if (!run_gemm_thin<gemm::CP_SC1>(a, S, r, ring, ready, next, nxt)) return false;
+    } else {
+      if (!ready()) return false;
+      nxt = run_gemm<FEW, gemm::CP_SC1>(a, S, r, ring, next);
+    }
     __builtin_amdgcn_s_waitcnt(0);
     if (threadIdx.x == 0) W.bc[1] = nxt;
     __syncthreads();  // every thread's output stores have completed
@@ -872,7 +930,7 @@ __device__ __forceinline__ bool compute_tiles(const FwdArgs& a, const Sched& S, 
     // of one, after it reduced the tile): its row tile gains a column
     bool publish = true;
     if (r.ph == 1 && a.nsplit > 1) {
-      publish = arrive_and_reduce<gemm::CP_SC1>(a, S, W, r, id);
+      publish = arrive_and_reduce<FEW, gemm::CP_SC1>(a, S, W, r, id);
       if (publish) {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -947,6 +1005,7 @@ __device__ __forceinline__ bool combine_claimed(const FwdArgs& a, const Sched& S
 // ===========================================================================
 // One layer, run by this workgroup.  next: the following layer of a
 // stacked launch, whose dispatch the movement workers start.
+template <bool FEW>
 __device__ __forceinline__ void mega_layer(const FwdArgs& a, Sched& S, Scratch& W, char* ring, const FwdArgs* next) {
   const int tid = threadIdx.x;
   const uint64_t t_entry = a.trace ? now_ticks() : 0;
@@ -990,7 +1049,6 @@ __device__ __forceinline__ void mega_layer(const FwdArgs& a, Sched& S, Scratch& 
       dispatch_one<true>(a, &S, W, u0, unit_row(a, &S, u0));
   }
 
-  bool ok = true;
   if (mover) {
     // dispatch: every token row, in token (hence chunk) order
     dispatch_claimed(a, S, W);
@@ -998,18 +1056,19 @@ __device__ __forceinline__ void mega_layer(const FwdArgs& a, Sched& S, Scratch& 
     if (a.trace && tid == 0) trace_rec(a, W, 3, ticket, 0, t_sched, now_ticks(), 0);
     // the next layer's dispatch beside this layer's GEMMs
     if (next) dispatch_ahead(*next, W);
-    // bubble stealing: n_steal GEMM tiles right after dispatch (section 3.2.2)
-    ok = compute_tiles(a, S, W, ring, ticket, S.n_steal);
-    if (ok) combine_claimed(a, S, W, ticket);
-  } else {
-    ok = compute_tiles(a, S, W, ring, ticket, 1 << 30);
-    // the final combine on every worker (section 4): once the compute queue
-    // is empty a compute worker joins the combine; in a stacked launch with a
-    // layer after this one it goes on to that layer's GEMMs instead, and this
-    // layer's movement workers combine meanwhile (on a few CUs a copy moves
-    // more bytes per CU than on all of them)
-    if (ok && S.final_all && !a.stack_next) combine_claimed(a, S, W, ticket);
   }
+  // compute workers take tiles until none is left, movement workers n_steal of
+  // them right after dispatch (bubble stealing, section 3.2.2).  One call for
+  // both: two inlined copies of the tile loop are twice the code to fetch.
+  // (n_steal counts whole-slab tiles)
+  const bool ok = compute_tiles<FEW>(a, S, W, ring, ticket,
+                                     mover ? min(S.n_steal, 1 << 28) * (FEW ? BN / S.bn[0] : 1) : 1 << 30);
+  // the final combine on every worker (section 4): once the compute queue is
+  // empty a compute worker joins the combine; in a stacked launch with a
+  // layer after this one it goes on to that layer's GEMMs instead, and this
+  // layer's movement workers combine meanwhile (on a few CUs a copy moves
+  // more bytes per CU than on all of them)
+  if (ok && (mover || (S.final_all && !a.stack_next))) combine_claimed(a, S, W, ticket);
   if (a.trace) {
     __syncthreads();
     if (tid == 0) trace_rec(a, W, 1, ticket, mover ? 1 : 0, t_entry, t_sched, now_ticks());
@@ -1026,12 +1085,18 @@ __device__ __forceinline__ void mega_layer(const FwdArgs& a, Sched& S, Scratch& 
   }
 }
 
-__global__ void __launch_bounds__(FNTH, 1) moe_megakernel(FwdArgs a) {
+template <bool FEW>
+__device__ __forceinline__ void mega_one(const FwdArgs& a) {
   __shared__ Sched S;
   __shared__ Scratch W;
   __shared__ __attribute__((aligned(1024))) char ring[gemm::RING_BYTES];
-  mega_layer(a, S, W, ring, nullptr);
+  mega_layer<FEW>(a, S, W, ring, nullptr);
 }
+
+// The _few kernels run layers of few rows (FwdArgs::gather) too; the others
+// hold only the whole-slab code, whose tiles run 2% slower in the longer kernel.
+__global__ void __launch_bounds__(FNTH, 1) moe_megakernel(FwdArgs a) { mega_one<false>(a); }
+__global__ void __launch_bounds__(FNTH, 1) moe_megakernel_few(FwdArgs a) { mega_one<true>(a); }
 
 // Several independent layers (they share x, not their outputs) in one
 // persistent launch: a workgroup moves on to layer l + 1 as soon as it finds
@@ -1042,18 +1107,27 @@ __global__ void __launch_bounds__(FNTH, 1) moe_megakernel(FwdArgs a) {
 // The layers' argument blocks are read in place from the kernel argument
 // segment (constant memory, scalar loads): indexing the by-value parameter
 // with the layer number would copy it to scratch.
-__global__ void __launch_bounds__(FNTH, 1) moe_megakernel_stack(StackArgs st) {
+template <bool FEW>
+__device__ __forceinline__ void mega_stack() {
   __shared__ Sched S;
   __shared__ Scratch W;
   __shared__ __attribute__((aligned(1024))) char ring[gemm::RING_BYTES];
-  (void)st;
   const __attribute__((address_space(4))) StackArgs* ka =
       (const __attribute__((address_space(4))) StackArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   const int n = ka->n;
   for (int l = 0; l < n; ++l) {
     __syncthreads();  // the previous layer's LDS state is dead
-    mega_layer(*(const FwdArgs*)&ka->layer[l], S, W, ring, l + 1 < n ? (const FwdArgs*)&ka->layer[l + 1] : nullptr);
+    mega_layer<FEW>(*(const FwdArgs*)&ka->layer[l], S, W, ring,
+                    l + 1 < n ? (const FwdArgs*)&ka->layer[l + 1] : nullptr);
   }
+}
+__global__ void __launch_bounds__(FNTH, 1) moe_megakernel_stack(StackArgs st) {
+  (void)st;
+  mega_stack<false>();
+}
+__global__ void __launch_bounds__(FNTH, 1) moe_megakernel_few_stack(StackArgs st) {
+  (void)st;
+  mega_stack<true>();
 }
 
 // ===========================================================================
@@ -1067,7 +1141,7 @@ __global__ void __launch_bounds__(FNTH, 1) serial_dispatch_kernel(FwdArgs a) {
   dispatch_static(a, W, blockIdx.x * NWF + wave_id(), gridDim.x * NWF);
 }
 
-template <int PH>
+template <int PH, bool FEW>
 __device__ __forceinline__ void serial_gemm(const FwdArgs& a) {
   __shared__ Sched S;
   __shared__ Scratch W;
@@ -1081,22 +1155,31 @@ __device__ __forceinline__ void serial_gemm(const FwdArgs& a) {
   int t = __builtin_amdgcn_readfirstlane(W.bc[1]);
   __syncthreads();
   while (t >= 0) {
-    const TileRef r = decode_tile(a, S, t);
+    const TileRef r = decode_tile<FEW>(a, S, t);
     const bool split = PH == 1 && a.nsplit > 1;
     auto next = [&] { return claim_tile(a, S, a.qxs, PH, home, stage, exhausted); };
     // split partials are read by another workgroup within this kernel:
     // agent-coherent stores, drained before the arrival count
-    const int nxt = split ? run_gemm<gemm::CP_SC1>(a, S, r, ring, next) : run_gemm<gemm::CP_PLAIN>(a, S, r, ring, next);
+    auto ready = [] { return true; };
+    int nxt = -1;
+    if (FEW && S.bn[PH] != BN) {
+      if (split) run_gemm_thin<gemm::CP_SC1>(a, S, r, ring, ready, next, nxt);
+      else run_gemm_thin<gemm::CP_PLAIN>(a, S, r, ring, ready, next, nxt);
+    } else {
+      nxt = split ? run_gemm<FEW, gemm::CP_SC1>(a, S, r, ring, next) : run_gemm<FEW, gemm::CP_PLAIN>(a, S, r, ring, next);
+    }
     if (split) __builtin_amdgcn_s_waitcnt(0);
     if (threadIdx.x == 0) W.bc[1] = nxt;
     __syncthreads();
-    if (split) arrive_and_reduce<gemm::CP_PLAIN>(a, S, W, r, S.mb[r.q * S.nseg + r.seg] + r.mt);
+    if (split) arrive_and_reduce<FEW, gemm::CP_PLAIN>(a, S, W, r, S.mb[r.q * S.nseg + r.seg] + r.mt);
     t = __builtin_amdgcn_readfirstlane(W.bc[1]);  // rewritten only after the next mainloop's barriers
   }
 }
 
-__global__ void __launch_bounds__(FNTH, 1) serial_gemm0_kernel(FwdArgs a) { serial_gemm<0>(a); }
-__global__ void __launch_bounds__(FNTH, 1) serial_gemm1_kernel(FwdArgs a) { serial_gemm<1>(a); }
+__global__ void __launch_bounds__(FNTH, 1) serial_gemm0_kernel(FwdArgs a) { serial_gemm<0, false>(a); }
+__global__ void __launch_bounds__(FNTH, 1) serial_gemm1_kernel(FwdArgs a) { serial_gemm<1, false>(a); }
+__global__ void __launch_bounds__(FNTH, 1) serial_gemm0_few_kernel(FwdArgs a) { serial_gemm<0, true>(a); }
+__global__ void __launch_bounds__(FNTH, 1) serial_gemm1_few_kernel(FwdArgs a) { serial_gemm<1, true>(a); }
 
 __global__ void __launch_bounds__(FNTH, 1) serial_combine_kernel(FwdArgs a) {
   __shared__ Scratch W;

@@ -4,11 +4,11 @@
 // A is either row-major (leading dimension lda) or group-tiled: 32-row
 // groups, each 32-deep k-step of a group one 2 KiB block (32 rows x 64
 // bytes), so a tile starting at any row reads whole lines too.  B, the packed
-// expert weights, is slab-tiled: a slab of 256 rows stores each 32-deep k-step as one 16 KiB
-// block (256 rows x 64 bytes), so a stage of B is one contiguous block and
-// every DMA instruction covers eight whole 128-byte lines instead of sixteen
-// half lines of 8 KiB-strided rows (measured at full chip: 10% less time per
-// k-step of the mainloop).  Slabs are padded to 256 rows, so B is never read
+// expert weights, is slab-tiled (common.h): a strip of 64 rows stores each
+// 32-deep k-step as one 4 KiB block (64 rows x 64 bytes), so every DMA
+// instruction covers eight whole 128-byte lines instead of sixteen half lines
+// of 8 KiB-strided rows (measured at full chip: 10% less time per k-step of
+// the mainloop).  Slabs are padded to 256 rows, so B is never read
 // out of bounds.
 //
 // Workgroup of 8 wave64s (2 per SIMD), wave grid 2 (rows) x 4 (columns), each
@@ -120,15 +120,22 @@ struct DmaOff {
 // elements per row), or group-tiled: `A` points at the group holding the
 // tile's first row, which is row r0 (0..31) of that group, and consecutive
 // groups are gstride bytes apart.
+// Row-major with `pair`: row r of the tile is row pair[r] / k of the matrix.
 struct AOp {
   const uint16_t* p;
   int lda, r0, gstride, rows;
+  const int32_t* pair;
+  int k;
 };
 constexpr int GROUP = 32;                      // rows per group of a group-tiled operand
 constexpr int GROUP_STEP = GROUP * KSTEP * 2;  // bytes per k-step block of a group
 
-__device__ __forceinline__ void dma_offsets(DmaOff& o, const AOp& A) {
-  const int lda = opaque(A.lda), a_rows = opaque(A.rows), r0 = opaque(A.r0), gs = opaque(A.gstride);
+constexpr int STRIP_STEP = STRIP * KSTEP * 2;  // bytes per k-step block of a weight strip
+
+// ldb: depth K of the packed matrix (its strips are K * 128 bytes apart)
+__device__ __forceinline__ void dma_offsets(DmaOff& o, const AOp& A, int ldb) {
+  ldb = opaque(ldb);
+  const int lda = opaque(A.lda), a_rows = opaque(A.rows), r0 = opaque(A.r0), gs = opaque(A.gstride), tk = opaque(A.k);
   const int lane = lane_here(), wave = opaque((int)(threadIdx.x >> 6));
 #pragma unroll
   for (int i = 0; i < A_INSTR; ++i) {
@@ -136,13 +143,14 @@ __device__ __forceinline__ void dma_offsets(DmaOff& o, const AOp& A) {
     const int row = g >> 2, c = (g & 3) ^ ((row >> 1) & 3);
     const int r = row < a_rows ? row : a_rows - 1;
     const int p = r0 + r;
-    o.a[i] = gs ? (uint32_t)((p >> 5) * gs + (p & (GROUP - 1)) * (KSTEP * 2) + c * 16) : (uint32_t)(r * lda + c * 8) * 2u;
+    if (A.pair) o.a[i] = (uint32_t)(A.pair[r] / tk) * (uint32_t)(lda * 2) + (uint32_t)(c * 16);
+    else o.a[i] = gs ? (uint32_t)((p >> 5) * gs + (p & (GROUP - 1)) * (KSTEP * 2) + c * 16) : (uint32_t)(r * lda + c * 8) * 2u;
   }
 #pragma unroll
   for (int i = 0; i < B_INSTR; ++i) {
     const int g = (wave * B_INSTR + i) * 64 + lane;
     const int row = g >> 2, c = (g & 3) ^ ((row >> 1) & 3);
-    o.b[i] = (uint32_t)(row * (KSTEP * 2) + c * 16);
+    o.b[i] = (uint32_t)((row / STRIP) * (ldb * (STRIP * 2)) + (row % STRIP) * (KSTEP * 2) + c * 16);
   }
 }
 
@@ -214,11 +222,11 @@ __device__ __forceinline__ void mfma_block(Acc& acc, const bf16x8_t (&af)[MB], c
 // instance passes the same barriers, so the waves of a workgroup may run
 // different instances; the DMA waits count this wave's own instructions.
 template <int MBA, bool ADMA>
-__device__ __forceinline__ void mainloop_mb(Acc& acc, const AOp& A, const uint16_t* B, int Kd, char* ring) {
+__device__ __forceinline__ void mainloop_mb(Acc& acc, const AOp& A, const uint16_t* B, int ldb, int Kd, char* ring) {
   constexpr int WI = ADMA ? INSTR : B_INSTR;  // DMA instructions of this wave per stage
   const int nk = Kd / KSTEP;
   DmaOff o;
-  dma_offsets(o, A);
+  dma_offsets(o, A, ldb);
   const int a_step = opaque(A.gstride) ? GROUP_STEP : KSTEP * 2;  // bytes from one k-step of A to the next
   // scalars of the DMA issue: this wave's destinations in stage 0 and the
   // operand bases, pinned in scalar registers
@@ -231,7 +239,7 @@ __device__ __forceinline__ void mainloop_mb(Acc& acc, const AOp& A, const uint16
   auto st = [&](int s) { return ring + (s & (NSTAGE - 1)) * STAGE_BYTES; };
   auto issue = [&](int s) {
     const uint32_t so = (uint32_t)((s & (NSTAGE - 1)) * STAGE_BYTES);
-    issue_stage<ADMA>(la0 + so, lb0 + so, Ab + (size_t)s * a_step, Bb + (size_t)s * B_BYTES, o);
+    issue_stage<ADMA>(la0 + so, lb0 + so, Ab + (size_t)s * a_step, Bb + (size_t)s * STRIP_STEP, o);
   };
   issue(0);
   if (nk > 1) issue(1);
@@ -269,13 +277,13 @@ __device__ __forceinline__ void mainloop_mb(Acc& acc, const AOp& A, const uint16
 }
 
 // acc += A[0..A.rows) . B^T over k in [0, Kd); Kd % 32 == 0.  B points at
-// the first k-step block of a 256-row slab of slab-tiled weights.
+// the first k-step block of a 256-row slab of slab-tiled weights of depth ldb.
 // ring: RING_BYTES of LDS.  Ends with a barrier (the ring may be reused).
 // A wave computes only the 32-row blocks of its rows that hold valid rows
 // (a_rows): the last row tile of an expert is often nearly empty, and its
 // padding rows would otherwise cost as much MFMA work as valid ones.  Their
 // accumulators stay zero and are never stored.
-__device__ __forceinline__ void mainloop(Acc& acc, const AOp& A, const uint16_t* B, int Kd, char* ring) {
+__device__ __forceinline__ void mainloop(Acc& acc, const AOp& A, const uint16_t* B, int ldb, int Kd, char* ring) {
   const int wave = opaque((int)(threadIdx.x >> 6)), wm = wave % WM;
   const int rows = opaque(A.rows);
   const int left = rows - wm * 32;  // valid rows from the wave's first block on
@@ -283,19 +291,19 @@ __device__ __forceinline__ void mainloop(Acc& acc, const AOp& A, const uint16_t*
   static_assert(A_INSTR * 16 == 32, "wave w's A DMA covers 32-row block w");
   if (rows > wave * 32) {
     switch (mba) {
-      case MB: mainloop_mb<MB, true>(acc, A, B, Kd, ring); break;
-      case 3: mainloop_mb<3, true>(acc, A, B, Kd, ring); break;
-      case 2: mainloop_mb<2, true>(acc, A, B, Kd, ring); break;
-      case 1: mainloop_mb<1, true>(acc, A, B, Kd, ring); break;
-      default: mainloop_mb<0, true>(acc, A, B, Kd, ring); break;
+      case MB: mainloop_mb<MB, true>(acc, A, B, ldb, Kd, ring); break;
+      case 3: mainloop_mb<3, true>(acc, A, B, ldb, Kd, ring); break;
+      case 2: mainloop_mb<2, true>(acc, A, B, ldb, Kd, ring); break;
+      case 1: mainloop_mb<1, true>(acc, A, B, ldb, Kd, ring); break;
+      default: mainloop_mb<0, true>(acc, A, B, ldb, Kd, ring); break;
     }
   } else {
     switch (mba) {
-      case MB: mainloop_mb<MB, false>(acc, A, B, Kd, ring); break;
-      case 3: mainloop_mb<3, false>(acc, A, B, Kd, ring); break;
-      case 2: mainloop_mb<2, false>(acc, A, B, Kd, ring); break;
-      case 1: mainloop_mb<1, false>(acc, A, B, Kd, ring); break;
-      default: mainloop_mb<0, false>(acc, A, B, Kd, ring); break;
+      case MB: mainloop_mb<MB, false>(acc, A, B, ldb, Kd, ring); break;
+      case 3: mainloop_mb<3, false>(acc, A, B, ldb, Kd, ring); break;
+      case 2: mainloop_mb<2, false>(acc, A, B, ldb, Kd, ring); break;
+      case 1: mainloop_mb<1, false>(acc, A, B, ldb, Kd, ring); break;
+      default: mainloop_mb<0, false>(acc, A, B, ldb, Kd, ring); break;
     }
   }
 }
@@ -484,6 +492,269 @@ __device__ __forceinline__ void store_f32(const Acc& acc, float* out, int ldo, i
                                                   (base + (uint32_t)(dr * ldo) + nb * 32) * 4u, 0, CP);
       }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Narrow tiles: up to 256 rows x 64 columns (a quarter of a weight slab; in
+// GEMM0 32 gate and their 32 up columns), for layers of so few rows that whole
+// slabs leave CUs without a tile.  The sums are those of the 256-column tile,
+// in the same order, so y has the same bits.  Wave w multiplies row block w
+// (32 rows) by both 32-column blocks; every wave loads.  A ring stage holds
+// THIN_KS k-steps while the tile has at most 64 rows (16 KiB of weights per
+// stage, as much in flight as the wide tile: a CU's stream is bound by the
+// bytes it has in flight, 48 KiB a microsecond), else one.  A tile has about
+// 6 us of fixed cost (first loads, epilogue, claim), so it pays only where
+// whole slabs fill half the CUs or fewer: routing and layer of 32 decode tokens of a
+// fine-grained layer (54 and 72 whole-slab tiles) 91 us with them, 84 us with
+// narrow ones.  The weights of the first stages are loaded before the wait for
+// the tile's inputs.
+// ---------------------------------------------------------------------------
+constexpr int THIN_KS = 4, THIN_ROWS = 64;
+
+typedef f32x16_t AccThin[NB];
+
+// A operand of a narrow tile: group-tiled from a group's first row (gstride
+// bytes from one 32-row group to the next), or (gstride 0) rows of ld bytes
+// of a row-major matrix, row r of the tile being first + r, or pair[r] / k.
+struct AThin {
+  const char* p;
+  int gstride, ld, first, k;
+  const int32_t* pair;
+  int rows;
+};
+
+template <int KS, bool ADMA, typename ReadyFn>
+__device__ __forceinline__ bool mainloop_thin_n(AccThin& acc, const AThin& A, const uint16_t* B, int Kd, char* ring,
+                                                ReadyFn&& ready) {
+  constexpr int RB = KS == THIN_KS ? THIN_ROWS / 32 : TILE_M / 32;  // row blocks of a stage
+  constexpr int A_ST = KS * RB * 2048, B_ST = KS * 4096, ST = A_ST + B_ST;
+  static_assert(NSTAGE * ST <= RING_BYTES, "narrow ring");
+  const int lane = lane_here(), wave = opaque((int)(threadIdx.x >> 6));
+  const int rows = opaque(A.rows), gs = opaque(A.gstride), ld = opaque(A.ld), first = opaque(A.first), tk = opaque(A.k);
+  const int nk = Kd / KSTEP, ns = (nk + KS - 1) / KS;
+  // this wave's DMA: k-step ks of a stage, A row block arb, B instructions
+  const int ks = KS == 1 ? 0 : wave >> 1, arb = KS == 1 ? wave : wave & 1;
+  constexpr int BI = KS == 1 ? 1 : 2;             // B instructions (KS = 1: of waves 0-3)
+  const int b0 = KS == 1 ? wave & 3 : (wave & 1) * 2;
+  uint32_t oa[2], ob[BI];
+#pragma unroll
+  for (int i = 0; i < BI; ++i) {
+    const int row = (b0 + i) * 16 + (lane >> 2);
+    ob[i] = (uint32_t)(row * (KSTEP * 2) + ((lane & 3) ^ ((row >> 1) & 3)) * 16);
+  }
+  const uint32_t ring0 = (uint32_t)opaque((int)lds_u32(ring));
+  const uint32_t la0 = ring0 + (uint32_t)((ks * RB + arb) * 2048), lb0 = ring0 + (uint32_t)(A_ST + ks * 4096 + b0 * 1024);
+  const char* Ab = opaque(A.p);
+  const char* Bb = opaque(reinterpret_cast<const char*>(B));
+  const int astep = gs ? GROUP_STEP : KSTEP * 2;
+  // (past the last k-step: loaded again, not multiplied)
+  auto issue_a = [&](int s) {
+    const uint32_t so = (uint32_t)((s & (NSTAGE - 1)) * ST);
+    if constexpr (ADMA) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) dma16(Ab + (size_t)min(s * KS + ks, nk - 1) * astep, oa[i], la0 + so + i * 1024);
+    }
+  };
+  auto issue_b = [&](int s) {
+    const uint32_t so = (uint32_t)((s & (NSTAGE - 1)) * ST);
+#pragma unroll
+    for (int i = 0; i < BI; ++i) dma16(Bb + (size_t)min(s * KS + ks, nk - 1) * STRIP_STEP, ob[i], lb0 + so + i * 1024);
+  };
+  constexpr int WI = (ADMA ? 2 : 0) + BI;
+  const bool mine = wave * 32 < rows;  // this wave has a row block
+  const int ra = wave * 32 + (lane & 31);
+  uint32_t fa[2], fb[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    const int c = kk * 2 + (lane >> 5);
+    fa[kk] = (uint32_t)swz(ra, c) * 16u;
+    fb[kk] = (uint32_t)(A_ST + swz(lane & 31, c) * 16);
+  }
+  // a whole stage: every fragment is read before the first product, so the
+  // one wave of a row block waits out the LDS latency once per stage
+  auto compute = [&](int s) {
+    const char* st = ring + (s & (NSTAGE - 1)) * ST;
+    bf16x8_t av[2 * KS], bv[2 * KS][NB];
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i) {
+      av[i] = *reinterpret_cast<const bf16x8_t*>(st + i / 2 * (RB * 2048) + fa[i & 1]);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) bv[i][nb] = *reinterpret_cast<const bf16x8_t*>(st + i / 2 * 4096 + fb[i & 1] + nb * 2048);
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * KS; ++i)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[i][nb], acc[nb], 0, 0, 0);
+  };
+  // the last stage, of nk - s KS k-steps
+  auto compute_rest = [&](int s) {
+    const char* st = ring + (s & (NSTAGE - 1)) * ST;
+#pragma unroll 1
+    for (int k = 0; k < nk - s * KS; ++k)
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        const bf16x8_t av = *reinterpret_cast<const bf16x8_t*>(st + k * (RB * 2048) + fa[kk]);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          const bf16x8_t bv = *reinterpret_cast<const bf16x8_t*>(st + k * 4096 + fb[kk] + nb * 2048);
+          acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[nb], 0, 0, 0);
+        }
+      }
+  };
+  // the weights of the first stages while the inputs become ready
+  issue_b(0);
+  if (ns > 1) issue_b(1);
+  if (ns > 2) issue_b(2);
+  if (!ready()) {
+    wait_vm<0>();
+    return false;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = arb * 32 + i * 16 + (lane >> 2), r = min(row, rows - 1);
+    uint32_t o;
+    if (gs) o = (uint32_t)((r >> 5) * gs + (r & 31) * (KSTEP * 2));
+    else o = (uint32_t)(A.pair ? A.pair[r] / tk : first + r) * (uint32_t)ld;
+    oa[i] = o + (uint32_t)(((lane & 3) ^ ((row >> 1) & 3)) * 16);
+  }
+  issue_a(0);
+  if (ns > 1) issue_a(1);
+  if (ns > 2) issue_a(2);
+  // The loop's waits count whole stages in order; A's loads of the first three
+  // follow all of their weights', so stages 0 and 1 are waited for here (only
+  // A's of stage 2 may be left, and it is within what stage 2's own wait counts)
+  if (ns > 2) wait_vm<ADMA ? 2 : 0>();
+  else wait_vm<0>();
+  int s = 0;
+  for (; s < ns - 3; ++s) {
+    wait_vm<2 * WI>();
+    __builtin_amdgcn_s_barrier();
+    compiler_fence();
+    issue_a(s + 3);
+    issue_b(s + 3);
+    if (mine) compute(s);
+  }
+  for (; s < ns; ++s) {
+    if (s + 2 < ns) wait_vm<2 * WI>();
+    else if (s + 1 < ns) wait_vm<WI>();
+    else wait_vm<0>();
+    __builtin_amdgcn_s_barrier();
+    compiler_fence();
+    if (mine) {
+      if (KS == 1 || (s + 1) * KS <= nk) compute(s);
+      else compute_rest(s);
+    }
+  }
+  __builtin_amdgcn_s_barrier();
+  compiler_fence();
+  return true;
+}
+
+// ready(): waits for the tile's inputs (every thread calls it; false: the
+// launch was aborted, and so is the tile)
+template <typename ReadyFn>
+__device__ __forceinline__ bool mainloop_thin(AccThin& acc, const AThin& A, const uint16_t* B, int Kd, char* ring,
+                                              ReadyFn&& ready) {
+  const int wave = opaque((int)(threadIdx.x >> 6)), rows = opaque(A.rows);
+  if (rows <= THIN_ROWS) {
+    if (!(wave & 1) || rows > 32) return mainloop_thin_n<THIN_KS, true>(acc, A, B, Kd, ring, ready);
+    else return mainloop_thin_n<THIN_KS, false>(acc, A, B, Kd, ring, ready);
+  } else {
+    if (wave * 32 < rows) return mainloop_thin_n<1, true>(acc, A, B, Kd, ring, ready);
+    else return mainloop_thin_n<1, false>(acc, A, B, Kd, ring, ready);
+  }
+}
+
+// Pairs of rows of a 32 x 32 block of wave-private values into `lds` as bf16
+// words of two adjacent columns (see stage_pairs), row stride in bytes
+template <typename ValFn>
+__device__ __forceinline__ void stage_block(char* lds, int stride, ValFn&& vals) {
+  const int lane = lane_here();
+  const bool odd = lane & 1;
+  const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    const uint32_t p = pack_bf16x2(vals(r), vals(r + 1));
+    const uint32_t w = __builtin_amdgcn_perm(swap_lane_pair(p), p, sel);
+    const int row = 4 * (lane >> 5) + 8 * (r >> 2) + (r & 3) + (odd ? 1 : 0);
+    *reinterpret_cast<uint32_t*>(lds + row * stride + ((lane & 31) & ~1) * 2) = w;
+  }
+}
+
+// GEMM0 epilogue of a narrow tile: wave w's 32 x 32 block of h is one block
+// of the group-tiled h (`out`: the tile's column block of its first 32-row
+// group, groups gs elements apart).  Only valid rows are stored.  Uses the
+// free ring; ends with an LDS barrier.
+template <int CP>
+__device__ __forceinline__ void store_silu_thin(const AccThin& acc, uint16_t* out, int gs, int out_rows, char* ring) {
+  const int lane = lane_here(), wave = opaque((int)(threadIdx.x >> 6));
+  gs = opaque(gs);
+  out_rows = opaque(out_rows);
+  constexpr int STRIDE = 64 + EPI_PAD;
+  char* lds = ring + wave * 32 * STRIDE;
+  const __amdgpu_buffer_rsrc_t rs = out_rsrc(out);
+  if (wave * 32 < out_rows) {
+    stage_block(lds, STRIDE, [&](int r) {
+      const float g = acc[0][r], u = acc[1][r];
+      return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+    });
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = i * 16 + (lane >> 2), c = (lane & 3) * 8;
+      if (wave * 32 + row < out_rows) {
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(lds + row * STRIDE + c * 2);
+        __builtin_amdgcn_raw_buffer_store_b128(v, rs, (uint32_t)(wave * gs + row * KSTEP + c) * 2u, 0, CP);
+      }
+    }
+  }
+  lds_barrier();
+}
+
+// GEMM1 epilogue of a narrow tile into a row-major O
+template <int CP>
+__device__ __forceinline__ void store_bf16_thin(const AccThin& acc, uint16_t* out, int ldo, int out_rows, char* ring) {
+  const int lane = lane_here(), wave = opaque((int)(threadIdx.x >> 6));
+  ldo = opaque(ldo);
+  out_rows = opaque(out_rows);
+  constexpr int STRIDE = 128 + EPI_PAD;
+  char* lds = ring + wave * 32 * STRIDE;
+  const __amdgpu_buffer_rsrc_t rs = out_rsrc(out);
+  if (wave * 32 < out_rows) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) stage_block(lds + nb * 64, STRIDE, [&](int r) { return acc[nb][r]; });
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = i * 8 + (lane >> 3), c = (lane & 7) * 8;
+      if (wave * 32 + row < out_rows) {
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(lds + row * STRIDE + c * 2);
+        __builtin_amdgcn_raw_buffer_store_b128(v, rs, (uint32_t)((wave * 32 + row) * ldo + c) * 2u, 0, CP);
+      }
+    }
+  }
+  lds_barrier();
+}
+
+// GEMM1 split-K epilogue of a narrow tile: this split's fp32 partial
+template <int CP>
+__device__ __forceinline__ void store_f32_thin(const AccThin& acc, float* out, int ldo, int out_rows) {
+  const int lane = lane_here(), wave = opaque((int)(threadIdx.x >> 6));
+  ldo = opaque(ldo);
+  const __amdgpu_buffer_rsrc_t rs = out_rsrc(out);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = wave * 32 + 4 * (lane >> 5) + 8 * (r >> 2) + (r & 3);
+    if (row < out_rows) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[nb][r]), rs,
+                                              (uint32_t)(row * ldo + nb * 32 + (lane & 31)) * 4u, 0, CP);
+    }
+  }
 }
 
 }  // namespace gemm

@@ -76,7 +76,8 @@ struct TableArgs {
   int T, Tr, R, k, E, e0, El;
   int cb, nblk;        // tokens per count block (blk_cnt, blk_bad), a power of two <= TAB_TB, and count blocks
   int scanned;         // blk_off and off hold tab_scan_kernel's result (else the table blocks sum blk_cnt)
-  int S, nt0, g1;      // shared experts; GEMM0 and GEMM1 tiles of one row tile
+  int S, wide0, wide1; // shared experts; GEMM0 column tiles, GEMM1 (column tile, split) pairs in whole slabs (BN columns)
+  int few, nsplit;     // narrow tiles may be chosen (few rows per expert); split-K factor of GEMM1
   int dt, ct;          // tokens per dispatch and combine unit
   int H, F, N;         // the cost model's shape and worker count
 };
@@ -127,6 +128,8 @@ struct Sched {
   int disp0;                  // dispatch units [0, disp0) are owned statically (megakernel)
   int K, nseg;                // chunks, segments
   int n_disp, n_comb;         // movement units
+  int nt[2];                  // column tiles of GEMM0 (over 2F) and GEMM1 (over H)
+  int bn[2];                  // their widths: BN, or THIN_N (narrow tiles)
   int bnd[MAX_K + 4];         // chunk token boundaries ceil(q*T/K), q <= K
   // per (chunk q, segment) at index q*nseg + seg
   int rows[MAX_K * MAX_SEG];
@@ -150,13 +153,14 @@ constexpr int SCHED_IMG0 = 4;                          // first word of the imag
 
 struct FwdArgs {
   // shape
-  int T, Tr, R, H, F, k, El, S, e0, N;
-  int nt0, nt1;   // column tiles of GEMM0 (over 2F) and GEMM1 (over H)
+  int T, Tr, H, F, k, El, S, e0;
+  int nt0, nt1;   // column tiles of GEMM0 (over 2F) and GEMM1 (over H); layers of few rows: Sched::nt counts, nt1 at most
+  int gather;     // few rows per expert: GEMM0 reads the routed rows straight from x and does not wait for
+                  // their dispatch, and a phase may run in narrow tiles (Sched::nt)
   int nsplit;     // split-K factor of GEMM1 (1, 2, 4 or 8)
   int dt, ct;     // tokens per dispatch unit (<= DT) and per combine unit (<= CT)
   int move_steal; // compute workers copy dispatch units while their rows are not
                   // ready (dynamic mode; the static split keeps its roles fixed)
-  int xmax;       // routed pairs at most (T * min(k, E_l))
   int mt_max;     // capacity of the per-row-tile counters
   int ctl_words;  // int32 words per control set
   int qx, qxs;    // word offsets of the [2 MAX_K][NXCD] tile queue heads (megakernel, serial GEMMs)
@@ -170,6 +174,7 @@ struct FwdArgs {
   uint16_t* y;
   // routing tables
   const int32_t* slot;
+  const int32_t* inv;      // pair g*k + j of each slot
   const int32_t* sub_off;
   const int32_t* row_off;  // [KOPT][E_l + S][SUBW] first row of each (segment, chunk) in A / Hbuf / O
   const int32_t* sched;    // [KOPT][SCHED_WORDS] schedule images (written by the table builder), K = 1, 2, 4, 8
@@ -321,9 +326,13 @@ __global__ void pack_transpose_kernel(PackArgs a);
 __global__ void pack_pad_kernel(PadArgs a);
 __global__ void moe_megakernel(FwdArgs a);
 __global__ void moe_megakernel_stack(StackArgs st);
+__global__ void moe_megakernel_few(FwdArgs a);
+__global__ void moe_megakernel_few_stack(StackArgs st);
 __global__ void serial_dispatch_kernel(FwdArgs a);
 __global__ void serial_gemm0_kernel(FwdArgs a);
 __global__ void serial_gemm1_kernel(FwdArgs a);
+__global__ void serial_gemm0_few_kernel(FwdArgs a);
+__global__ void serial_gemm1_few_kernel(FwdArgs a);
 __global__ void serial_combine_kernel(FwdArgs a);
 
 }  // namespace moe

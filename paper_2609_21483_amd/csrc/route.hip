@@ -354,7 +354,7 @@ __global__ void __launch_bounds__(TBN + WAVE) tab_build_kernel(TableArgs a) {
 #pragma unroll 1
     for (int v = lane; v < n; v += WAVE) tiles += (seg_chunk_rows(a, so, ki, v >> ki, v & ((1 << ki) - 1)) + BM - 1) / BM;
     tiles = wave_incl_scan(tiles, lane);
-    if (lane == WAVE - 1) ntk[ki] = tiles * (a.nt0 + a.g1);
+    if (lane == WAVE - 1) ntk[ki] = tiles * (a.wide0 + a.wide1);
   }
   lds_sync();
   if (wave == NW) {
@@ -429,10 +429,19 @@ __global__ void __launch_bounds__(TBN + WAVE) tab_build_kernel(TableArgs a) {
     if (lane == 0) base[ki][K] = carry;
     wave_lds_sync();
     static_assert(NLVL == 1, "shared row tiles (level 0), then the routed ones");
+    // A layer of few rows takes the time of streaming its experts' weights.  A
+    // CU streams up to 47 GB/s and all of them together 5.9 TB/s, so whole-slab
+    // tiles for half the workers about fill HBM; fewer leave it idle, and
+    // narrow tiles do better in spite of their 6 us of fixed cost each.
+    // Routing and layer, whole slabs / narrow tiles: GEMM1 of 128 tiles on 256
+    // workers 210 / 199 us; GEMM1 of 144 tiles 127 / 133 us.
+    const bool thin0 = a.few && carry * a.wide0 * 2 <= a.N, thin1 = a.few && carry * a.wide1 * 2 <= a.N;
+    const int nt0 = thin0 ? ceil_div(2 * a.F, THIN_N) : a.wide0;
+    const int nt1 = thin1 ? ceil_div(a.H, THIN_N) : ceil_div(a.H, BN);
 #pragma unroll 1
     for (int v = lane; v < 2 * K * NXCD; v += WAVE) {
       const int stage = v / NXCD, x = v % NXCD, qp = stage_qph(stage, K), q = qp >> 1;
-      img->ncls[stage][x] = class_slabs(qp & 1 ? a.g1 : a.nt0, x) * (base[ki][q + 1] - base[ki][q]);
+      img->ncls[stage][x] = class_slabs(qp & 1 ? nt1 * a.nsplit : nt0, x) * (base[ki][q + 1] - base[ki][q]);
     }
     if (lane < K) {
       img->lvl[lane][0] = a.S ? a.S * ((seg_chunk_rows(a, so, ki, El, lane) + BM - 1) / BM) : 0;
@@ -440,6 +449,10 @@ __global__ void __launch_bounds__(TBN + WAVE) tab_build_kernel(TableArgs a) {
     }
     if (lane <= K) img->bnd[lane] = chunk_bnd(T, ki, lane);
     if (lane == 0) {
+      img->nt[0] = nt0;
+      img->nt[1] = nt1;
+      img->bn[0] = thin0 ? THIN_N : BN;
+      img->bn[1] = thin1 ? THIN_N : BN;
       img->K = K;
       img->nseg = nseg;
       img->n_disp = ceil_div(T, a.dt);

@@ -143,6 +143,53 @@ def test_gemm1_split_factors(B, split):
     check_case(B, c, forced=[(8, 2, 3, 1), (100, 4, 0, 0)], gemm1_split=split)
 
 
+@pytest.mark.parametrize("shape,skew,split", [
+    (W.MoeShape("few32", 90, 2, 40, 192, 192, 16, 2, 4), 0, 1),           # one row block, ragged columns
+    (W.MoeShape("few64", 89, 3, 64, 128, 192, 8, 2, 8, n_shared_experts=1), 0, 2),  # two; rank 0 fills a shared one
+    (W.MoeShape("few_skew", 88, 2, 192, 128, 320, 32, 4, 6), 1, 1),      # one expert takes every token: 256 rows + 128
+    (W.MoeShape("few_wide", 87, 1, 64, 128, 512, 48, 8, 40), 0, 4),      # GEMM0 in whole slabs, GEMM1 in narrow tiles
+    (W.MoeShape("few_wide_skew", 86, 1, 384, 320, 512, 64, 8, 48), 1, 1),
+], ids=lambda v: getattr(v, "name", None))
+def test_few_rows(B, shape, skew, split):
+    """Layers of at most 48 routed rows per expert gather their rows and run
+    phases of few tiles in narrow ones: y matches the oracle and has the bits
+    of the general path, which a layer of the same tokens and routing several
+    times over takes (a token's y does not depend on the other tokens)."""
+    shape = shape.with_(w_std=0.05)
+    c = make_case(shape)
+    R, Tr, H, E, k = shape.n_src_ranks, shape.tokens_per_rank, shape.hidden, shape.n_experts, shape.top_k
+    idx, w = W.random_routing(shape.T, E - skew, k - skew, seed=7)
+    if skew:
+        idx = np.concatenate([np.zeros((shape.T, 1), np.int64), idx + 1], axis=1)
+        w = np.concatenate([np.full((shape.T, 1), 0.5), w * 0.5], axis=1)
+    idx, w = idx.astype(np.int32), w.astype(np.float32)
+    rep = 48 * E // (shape.T * k) + 1
+    assert shape.T * k <= 48 * E < rep * shape.T * k
+    big = shape.with_(tokens_per_rank=Tr * rep)
+
+    def again(a):  # each rank's tokens rep times
+        return np.tile(a.reshape(R, Tr, -1), (1, rep, 1)).reshape(R * Tr * rep, -1)
+
+    layers = [B.MoeLayer(s, c.w1, c.w3, c.w2, c.ws1, c.ws3, c.ws2, gemm1_split=split) for s in (shape, big)]
+    try:
+        outs = run_modes(B, layers[0], c, idx, w, forced=[(8, 2, 3, 1), (100, 4, 0, 0)])
+        y = outs["dynamic"]
+        for key, o in outs.items():
+            assert torch.equal(o.view(torch.int16), y.view(torch.int16)), key
+        assert rel_err(bf16_to_f64(y), oracle_rows(c, idx, w.astype(np.float64), np.arange(shape.T))) <= TOL
+        x2 = c.x.view(R, Tr, H).repeat(1, rep, 1).reshape(-1, H).contiguous().cuda()
+        idx2, w2 = torch.from_numpy(again(idx)).cuda(), torch.from_numpy(again(w)).cuda()
+        y2 = torch.empty((big.T, H), dtype=torch.bfloat16, device="cuda")
+        B.moe_build_tables(layers[1].h, idx2)
+        layers[1].forward(x2, idx2, w2, y2, "dynamic")
+        assert B.moe_sync_status(layers[1].h) == B.MOE_OK
+        y2 = y2.view(R, Tr * rep, H)[:, :Tr].reshape(-1, H)
+        assert torch.equal(y2.contiguous().view(torch.int16), y.view(torch.int16))
+    finally:
+        for layer in layers:
+            layer.close()
+
+
 def test_no_local_pairs(B):
     """Every token routed off this GPU: y must be all zeros (no shared experts),
     or only the shared output on rank 0."""
