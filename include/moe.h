@@ -256,9 +256,9 @@ moe_status moe_packed_weights_size(const moe_handle* h, size_t* bytes);
 
 /* Packs the expert weights into the GEMM operand layout (not part of the
  * layer; done once): each matrix is transposed to k-contiguous rows and
- * stored as 256-row slabs, one 256 x 32 block per 32-deep k-step, so that
+ * stored as strips of 64 rows, one 64 x 32 block per 32-deep k-step, so that
  * the GEMM tiles stream whole blocks.  The layout is internal to the
- * library.  w1, w3: bf16 [E_l][H][F] (gate, up), w2: bf16
+ * library: a packed buffer is for the build that wrote it.  w1, w3: bf16 [E_l][H][F] (gate, up), w2: bf16
  * [E_l][F][H] (down); ws1, ws3, ws2 the same for the S shared experts (NULL
  * when S = 0).  packed: device buffer of moe_packed_weights_size bytes. */
 moe_status moe_pack_weights(moe_handle* h, const uint16_t* w1, const uint16_t* w3,
