@@ -68,6 +68,40 @@ def test_stack_matches_single_launches_and_oracle(B, shape, n_layers, mode):
             ml.close()
 
 
+@pytest.mark.parametrize("plan", [None, (8, 2, 3, 1)], ids=["model", "K2"])
+def test_stack_of_few_row_layers(B, plan):
+    """A stack that holds a layer of few rows runs the few-row kernel for all
+    of its layers: narrow tiles, whole slabs of gathered rows, and a general
+    layer between them give the bits of their single launches."""
+    shapes = [W.MoeShape(n, 80 + i, 2, 64, 128, F, E, 2, E, w_std=0.05)
+              for i, (n, F, E) in enumerate([("narrow", 64, 32), ("general", 192, 4), ("slabs", 640, 32)])]
+    cases = [make_case(s) for s in shapes]
+    layers = [B.MoeLayer(s, c.w1, c.w3, c.w2) for s, c in zip(shapes, cases)]
+    try:
+        T, H = shapes[0].T, shapes[0].hidden
+        x = cases[0].x.cuda()
+        forced = None if plan is None else B.moe_plan(*plan, 0.0)
+        idx, w, singles = [], [], []
+        for s, ml in zip(shapes, layers):
+            i, ww = W.random_routing(T, s.n_experts, s.top_k, seed=s.ffn)
+            idx.append(torch.from_numpy(i).cuda())
+            w.append(torch.from_numpy(ww).cuda())
+            B.moe_build_tables(ml.h, idx[-1])
+            singles.append(torch.empty((T, H), dtype=torch.bfloat16, device="cuda"))
+            ml.forward(x, idx[-1], w[-1], singles[-1], "serial")
+            assert B.moe_sync_status(ml.h) == B.MOE_OK
+        for rep in range(2):  # twice: both control sets of every layer
+            ys = [torch.full((T, H), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in layers]
+            B.moe_forward_stack([ml.h for ml in layers], x, idx, w, [ml.packed for ml in layers], ys,
+                                B.MOE_MODE_DYNAMIC, forced)
+            for l, ml in enumerate(layers):
+                assert B.moe_sync_status(ml.h) == B.MOE_OK, (rep, l, B.moe_last_error())
+                assert torch.equal(ys[l].view(torch.int16), singles[l].view(torch.int16)), (rep, l)
+    finally:
+        for ml in layers:
+            ml.close()
+
+
 @pytest.mark.parametrize("plan", [(8, 2, 3, 1), (4, 4, 0, 0), "stale"], ids=["K2", "K4", "stale-calibration"])
 def test_stack_dispatch_ahead_plans(B, plan):
     """A layer's movement workers dispatch the next layer ahead under that
