@@ -383,7 +383,7 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
   a.nt0 = h->nt0;
   a.nt1 = h->few ? (h->cfg.hidden + THIN_N - 1) / THIN_N : h->nt1;
   a.nsplit = h->nsplit;
-  a.gather = h->few;
+  a.gather = h->few && mode != MOE_MODE_SERIAL;  // (a separate GEMM0 reads what the dispatch stage wrote)
   move_units(h, &a.dt, &a.ct);
   a.mt_max = h->mt_max;
   a.ctl_words = h->ctl_words;

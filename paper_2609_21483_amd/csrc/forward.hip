@@ -579,10 +579,11 @@ __device__ __forceinline__ int claim_tile(const FwdArgs& a, const Sched& S, int 
   return -1;
 }
 
-// A narrow tile (gemm::mainloop_thin).  GEMM0 takes routed rows straight from
-// x (row r of the tile is token inv[slot] / k).
+// A narrow tile (gemm::mainloop_thin).  GATHER: in a launch that gathers
+// (FwdArgs::gather), GEMM0 takes routed rows straight from x (row r of the tile
+// is token inv[slot] / k); else, and in the separate kernels, from A.
 // Returns false when the launch was aborted.
-template <int CP, typename ReadyFn, typename ClaimFn>
+template <bool GATHER, int CP, typename ReadyFn, typename ClaimFn>
 __device__ __forceinline__ bool run_gemm_thin(const FwdArgs& a, const Sched& S, const TileRef& r, char* ring,
                                               ReadyFn&& ready, ClaimFn&& claim_next, int& nxt) {
   const int qs = r.q * S.nseg + r.seg;
@@ -596,7 +597,15 @@ __device__ __forceinline__ bool run_gemm_thin(const FwdArgs& a, const Sched& S, 
   int Kd;
   if (r.ph == 0) {
     const int first = S.sbase[qs] + r.mt * BM;  // slot (routed) or token (shared) of the tile's first row
-    A = {reinterpret_cast<const char*>(a.x), 0, a.H * 2, first, a.k, r.seg < a.El ? a.inv + first : nullptr, r.rows};
+    if (r.seg >= a.El) {
+      A = {reinterpret_cast<const char*>(a.x), 0, a.H * 2, first, 1, nullptr, r.rows};
+    } else if (GATHER && a.gather) {
+      A = {reinterpret_cast<const char*>(a.x), 0, a.H * 2, 0, a.k, a.inv + first, r.rows};
+    } else {
+      const size_t arow = (size_t)S.arow0[qs] + (size_t)r.mt * BM;
+      A = {reinterpret_cast<const char*>(a.A + (arow >> 5) * (size_t)a.H * gemm::GROUP), a.H * gemm::GROUP * 2, 0, 0, 1,
+           nullptr, r.rows};
+    }
     B = a.w13 + (size_t)r.seg * slab_rows(2 * a.F) * a.H + (size_t)n0 * a.H;
     Kd = a.H;
   } else {
@@ -622,7 +631,7 @@ __device__ __forceinline__ bool run_gemm_thin(const FwdArgs& a, const Sched& S, 
 // Thread 0 claims the next tile (claim_next) between the mainloop and the
 // epilogue (returned on thread 0), so the claim's round trip overlaps the
 // epilogue stores.
-template <bool FEW, int CP, typename ClaimFn>
+template <bool GATHER, int CP, typename ClaimFn>
 __device__ __forceinline__ int run_gemm(const FwdArgs& a, const Sched& S, const TileRef& r, char* ring,
                                         ClaimFn&& claim_next) {
   const int qs = r.q * S.nseg + r.seg;
@@ -640,7 +649,7 @@ __device__ __forceinline__ int run_gemm(const FwdArgs& a, const Sched& S, const 
     const size_t arow = (size_t)S.arow0[qs] + (size_t)r.mt * BM;
     if (r.seg >= a.El) {
       A = {a.x + arow * a.H, a.H, 0, 0, r.rows, nullptr, 1};
-    } else if (FEW && a.gather) {
+    } else if (GATHER && a.gather) {
       A = {a.x, a.H, 0, 0, r.rows, a.inv + S.sbase[qs] + r.mt * BM, a.k};
     } else {
       A = {a.A + (arow >> 5) * (size_t)a.H * gemm::GROUP, a.H, (int)(arow & 31), a.H * gemm::GROUP * 2, r.rows, nullptr, 1};
@@ -918,7 +927,7 @@ __device__ __forceinline__ bool compute_tiles(const FwdArgs& a, const Sched& S, 
     auto next = [&] { return more ? claim_tile(a, S, a.qx, -1, home, stage, exhausted) : -1; };
     int nxt = -1;
     if (FEW && S.bn[r.ph] != BN) {
-      if (!run_gemm_thin<gemm::CP_SC1>(a, S, r, ring, ready, next, nxt)) return false;
+      if (!run_gemm_thin<true, gemm::CP_SC1>(a, S, r, ring, ready, next, nxt)) return false;
     } else {
       if (!ready()) return false;
       nxt = run_gemm<FEW, gemm::CP_SC1>(a, S, r, ring, next);
@@ -1163,10 +1172,10 @@ __device__ __forceinline__ void serial_gemm(const FwdArgs& a) {
     auto ready = [] { return true; };
     int nxt = -1;
     if (FEW && S.bn[PH] != BN) {
-      if (split) run_gemm_thin<gemm::CP_SC1>(a, S, r, ring, ready, next, nxt);
-      else run_gemm_thin<gemm::CP_PLAIN>(a, S, r, ring, ready, next, nxt);
+      if (split) run_gemm_thin<false, gemm::CP_SC1>(a, S, r, ring, ready, next, nxt);
+      else run_gemm_thin<false, gemm::CP_PLAIN>(a, S, r, ring, ready, next, nxt);
     } else {
-      nxt = split ? run_gemm<FEW, gemm::CP_SC1>(a, S, r, ring, next) : run_gemm<FEW, gemm::CP_PLAIN>(a, S, r, ring, next);
+      nxt = split ? run_gemm<false, gemm::CP_SC1>(a, S, r, ring, next) : run_gemm<false, gemm::CP_PLAIN>(a, S, r, ring, next);
     }
     if (split) __builtin_amdgcn_s_waitcnt(0);
     if (threadIdx.x == 0) W.bc[1] = nxt;

@@ -295,6 +295,40 @@ def test_run_stages_reproduces_forward(B, K):
         ml.close()
 
 
+@pytest.mark.parametrize("shape", [
+    W.MoeShape("few_stages", 85, 2, 40, 192, 192, 16, 2, 4),          # narrow tiles of one row block
+    W.MoeShape("few_stages_wide", 84, 1, 64, 128, 512, 48, 8, 40),    # GEMM0 in whole slabs
+    W.MoeShape("few_stages_tall", 83, 2, 192, 128, 320, 16, 1, 1),    # one expert of many rows: one k-step a stage
+    W.MoeShape("general_stages", 82, 2, 300, 128, 192, 4, 2, 2),
+], ids=lambda s: s.name)
+@pytest.mark.parametrize("K", [1, 4])
+def test_run_stages_read_what_earlier_stages_wrote(B, shape, K):
+    """Stages called one by one, x overwritten once its rows are dispatched:
+    GEMM0 reads the dispatched rows, also in layers of few rows."""
+    c = make_case(shape.with_(w_std=0.05))
+    idx, w = W.random_routing(shape.T, shape.n_experts, shape.top_k, seed=11)
+    if shape.name == "few_stages_tall":
+        idx[:] = 0
+    idx, w = idx.astype(np.int32), w.astype(np.float32)
+    ml = B.MoeLayer(shape, c.w1, c.w3, c.w2)
+    try:
+        x, idx_d, w_d = c.x.cuda(), torch.from_numpy(idx).cuda(), torch.from_numpy(w).cuda()
+        B.moe_build_tables(ml.h, idx_d)
+        y0 = torch.empty((shape.T, shape.hidden), dtype=torch.bfloat16, device="cuda")
+        ml.forward(x, idx_d, w_d, y0, "dynamic")
+        assert rel_err(bf16_to_f64(y0), oracle_rows(c, idx, w.astype(np.float64), np.arange(shape.T))) <= TOL
+        n = torch.cuda.get_device_properties(0).multi_processor_count
+        y = torch.full_like(y0, float("nan"))
+        for stage in (1, 2, 4, 8):
+            B.moe_run_stages(ml.h, x, idx_d, w_d, ml.packed, y, stage, n, K)
+            if stage == 1:
+                x.zero_()
+        assert B.moe_sync_status(ml.h) == B.MOE_OK
+        assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
+    finally:
+        ml.close()
+
+
 def test_route_then_forward_end_to_end(B):
     """moe_route output fed straight into moe_forward."""
     shape = W.FINE_ZIPF.with_(tokens_per_rank=256)
