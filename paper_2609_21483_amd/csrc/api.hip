@@ -299,10 +299,20 @@ bool gate_counts(const moe_handle* h) {
 // the fine-grained shape 91 -> 84 us, 64 of the Mixtral shape 210 -> 199).
 // These layers have kernels of their own: with this code in the one kernel
 // the tiles of large layers ran 2% slower.
+// Averages say nothing about the routing, and the movement workers copy the
+// rows by themselves, so a layer is general where their copy could outlast the
+// GEMMs: beyond FEW_TOKENS tokens or FEW_BYTES of rows, if every token chose
+// local experts only.  Gathering against general, us: 24000 tokens, all for
+// one of 8 local experts of 512 (H = F = 1024, 49 MB), 330 : 240; 1024 tokens
+// over 16 of 256 (H = 7168, F = 2048, k = 8, at most 117 MB, 7 MB here)
+// 361 : 349; 4096 tokens, all for one (8 MB), 88 : 87; 768 tokens over 32 of
+// 128 (H = 2048, F = 768, k = 8, at most 25 MB) 126 : 130.
+constexpr long long FEW_TOKENS = 4096, FEW_BYTES = 24LL << 20;
+constexpr int GATHER_UNITS = 256;  // dispatch units of a gathering launch, about
 int few_rows(const moe_config& c) {
   const long long T = (long long)c.n_src_ranks * c.tokens_per_rank;
   return T * c.top_k <= (long long)FEW_ROWS * c.n_experts && (c.n_shared_experts == 0 || c.tokens_per_rank <= 64) &&
-         T * c.hidden * 2 < (1LL << 32);
+         T <= FEW_TOKENS && T * std::min(c.top_k, c.n_local_experts) * c.hidden * 2 <= FEW_BYTES;
 }
 
 TableArgs table_args(moe_handle* h, const int32_t* topk_idx) {
@@ -413,9 +423,13 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
   a.plan_out = at<moe_plan>(h, h->lay.plan);
   a.calib = at<DevCalib>(h, h->off_calib);
   a.mode = mode;
-  // (rows gathered from x: nobody waits for the dispatch, the movement
-  // workers run it by themselves)
+  // (rows gathered from x: nobody waits for the dispatch, the movement workers
+  // run it by themselves, 8 to 16 of them as a rule, each wavefront a unit at a
+  // time: so few wavefronts take units of several tokens, as one token a unit,
+  // sized for all the workers, is bound by latency.  4096 tokens, all for one
+  // local expert (H = F = 1024): 130 us with units of 2 tokens, 88 of 8)
   a.move_steal = mode == MOE_MODE_DYNAMIC && !a.gather ? 1 : 0;
+  if (a.gather) a.dt = std::min(std::max(h->T / GATHER_UNITS, 1), DT);
   a.forced = forced ? 1 : 0;
   if (forced) a.fplan = *forced;
   a.timeout_ticks = h->timeout_ticks;

@@ -1038,6 +1038,7 @@ __device__ __forceinline__ void mega_layer(const FwdArgs& a, Sched& S, Scratch& 
     // the ticket's round trip overlapped the plan
     W.bc[0] = tk;
     W.ticket = tk;
+    if (FEW) S.n_disp = ceil_div(a.T, a.dt);  // (the image counts units for all the workers)
     S.disp0 = a.static_disp ? (a.move_steal ? ceil_div(S.bnd[1], a.dt) : min(S.n_disp, S.c * NWF)) : 0;
   }
   __syncthreads();

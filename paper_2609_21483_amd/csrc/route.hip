@@ -434,8 +434,12 @@ __global__ void __launch_bounds__(TBN + WAVE) tab_build_kernel(TableArgs a) {
     // tiles for half the workers about fill HBM; fewer leave it idle, and
     // narrow tiles do better in spite of their 6 us of fixed cost each.
     // Routing and layer, whole slabs / narrow tiles: GEMM1 of 128 tiles on 256
-    // workers 210 / 199 us; GEMM1 of 144 tiles 127 / 133 us.
-    const bool thin0 = a.few && carry * a.wide0 * 2 <= a.N, thin1 = a.few && carry * a.wide1 * 2 <= a.N;
+    // workers 210 / 199 us; GEMM1 of 144 tiles 127 / 133 us.  Tiles of more
+    // rows than a narrow one takes in its fast form (a skewed routing) pay only
+    // while every worker has at most one: of 256 rows each (H = 2048), 8 row
+    // tiles 117 / 92 us, 16 of them 123 / 143.
+    const int per = offs[El] + a.S * a.Tr > gemm::THIN_ROWS * carry ? BN / THIN_N : 2;
+    const bool thin0 = a.few && carry * a.wide0 * per <= a.N, thin1 = a.few && carry * a.wide1 * per <= a.N;
     const int nt0 = thin0 ? ceil_div(2 * a.F, THIN_N) : a.wide0;
     const int nt1 = thin1 ? ceil_div(a.H, THIN_N) : ceil_div(a.H, BN);
 #pragma unroll 1

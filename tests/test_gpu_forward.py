@@ -190,6 +190,31 @@ def test_few_rows(B, shape, skew, split):
             layer.close()
 
 
+@pytest.mark.parametrize("shape,spread,split", [
+    (W.MoeShape("few_units3", 81, 1, 770, 128, 1088, 17, 1, 8), 8, 1),     # tall row tiles, too many for narrow ones
+    (W.MoeShape("few_units3n", 80, 1, 770, 128, 960, 17, 1, 8), 8, 2),     # tall row tiles, narrow
+    (W.MoeShape("few_units4", 79, 2, 513, 192, 192, 86, 4, 20), 86, 1),    # dispatch units of 4 tokens, the last of 2
+    (W.MoeShape("few_units8", 78, 1, 4096, 64, 128, 86, 1, 3), 3, 1),      # the most tokens that gather, all local
+    (W.MoeShape("beyond_few", 77, 1, 4097, 64, 128, 86, 1, 3), 3, 1),      # one more
+], ids=lambda v: getattr(v, "name", None))
+def test_few_rows_under_skewed_routing(B, shape, spread, split):
+    """Layers of few rows on average whose routing takes `spread` experts: row
+    tiles taller than a narrow tile's fast range, dispatch units of several
+    tokens, and the bounds of the rule."""
+    c = make_case(shape.with_(w_std=0.05))
+    idx, w = W.random_routing(shape.T, spread, shape.top_k, seed=13)
+    idx, w = idx.astype(np.int32), w.astype(np.float32)
+    layer = B.MoeLayer(shape, c.w1, c.w3, c.w2, gemm1_split=split)
+    try:
+        outs = run_modes(B, layer, c, idx, w, forced=[(8, 2, 3, 1), (100, 4, 0, 0), (1, 1, 0, 1)])
+        for key, o in outs.items():
+            assert torch.equal(o.view(torch.int16), outs["serial"].view(torch.int16)), key
+        y_ref = oracle_rows(c, idx, w.astype(np.float64), np.arange(shape.T))
+        assert rel_err(bf16_to_f64(outs["serial"]), y_ref) <= TOL
+    finally:
+        layer.close()
+
+
 def test_no_local_pairs(B):
     """Every token routed off this GPU: y must be all zeros (no shared experts),
     or only the shared output on rank 0."""
