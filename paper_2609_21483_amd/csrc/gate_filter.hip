@@ -907,19 +907,57 @@ __global__ void __launch_bounds__(NTH) gate_final_kernel(FilterArgs a) {
 }
 
 // Where the filter is the faster gate: its matrix pass is bf16 and only k + 1
-// or so of a token's E chains are evaluated, but it is four kernels.  gate.hip
-// against this file, us, E = 128, k = 8: 8192 tokens 33 : 50 (H = 1024),
-// 51 : 73 (2048), 93 : 119 (4096); 16384 tokens 52 : 57, 84 : 86, 165 : 149;
-// 32768 tokens 95 : 77, 164 : 127, 308 : 228.  E = 72, k = 4: 16384 tokens
-// 44 : 48, 81 : 69, 156 : 117.  With fewer experts per token the chains are
-// fewer too, and above 128 experts both sides are slower: H = 4096, E = 126,
-// k = 2, 8192 and 16384 tokens 93 : 105 and 156 : 136; E = 256, k = 1, 161 :
-// 157 and 316 : 199; k = 8, 170 : 330 and 321 : 428; E = 510, k = 4, 8192
-// tokens 376 : 299.
+// or so of a token's E chains are evaluated, but it is four kernels with a
+// floor of 27 to 170 us.  The gate's time is a step function of T (rounds of
+// workgroups over the CUs, each a whole chain of H steps) and depends on E by
+// its class only, so the line between them is none of T * H: E = 128, k = 4,
+// H = 4096, gate : filter, us, 8192 tokens 92 : 129, 8200 156 : 130, 16384
+// 161 : 144, 16400 230 : 170; E = 260, k = 8, 16384 tokens 684 : 461; E = 130,
+// k = 2, 324 : 200; E = 256, k = 8, 10000 tokens 238 : 349.  So both times are
+// estimated (us) by formulas fitted to 25000 measured points (E 66 to 512, T
+// 512 to 131072, H 256 to 16384, k 1 to 8), and the smaller one decides: over
+// these points the choice is 0.2% slower than the better gate on average, by
+// more than 10% at 0.4% of them and by a third at most (H = 16384).  Up to 64
+// experts the gate was the faster one everywhere.
+static double gate_us(long long T, long long H, int E, int k) {
+  const GateGeometry g = gate_geometry((int)T, E);
+  const int cus = GATE_SIMDS / 4, wide = g.ec > 256;
+  const double h = (double)H;
+  if (!g.large) {
+    const bool two = (T + 3) / 4 * (g.ec / 64) > GATE_SIMDS;  // wavefronts per SIMD
+    return wide ? 11 + 0.021 * h : two ? 9.7 + 0.0169 * h : 9 + 0.011 * h;
+  }
+  const double r = (double)((g.grid + cus - 1) / cus);
+  return wide ? 1.4 + r * (5.3 + 0.0378 * h + 1.37 * k) : 5.6 + r * (1.9 + 0.017 * h + 0.42 * k) + 0.0032 * h;
+}
+
+static double filter_us(long long T, long long H, int E, int k) {
+  struct Coef {
+    double t64, t64h, t128, t128h;  // a round of tiles of 64 or 128 tokens: fixed, per H
+    double c, ck;                   // four launches; per expert chosen
+    double floor, chain;            // the chains: one of H steps; per 1e6 T k H, whichever is longer
+    double te, tk;                  // logits and candidates, per 1e6 T E; per 1e6 T k
+    double h4, h4tk, h8, h8tk;      // per 1000 H past 4096 and past 8192 (the chains' rows outgrow the L2s), the
+                                    // second of each also per 1e6 T k
+  };
+  static const Coef coef[3] = {
+      {-2.0, 0.015, -1.3, 0.0232, 25.6, -1.64, 0.0031, 0.388, 3.32, 35, 17.2, 161, 19.1, 607},  // E <= 128, k < 4
+      {0.95, 0.0119, 1.7, 0.0182, 16.7, 0.99, 0.0133, 0.103, 3.28, 17.5, -4.9, 130, -2.3, 210},  // E <= 128, k >= 4
+      {11.1, 0.0095, 26.2, 0.018, 28.4, 3.3, 0, 0.411, 6.0, 187, 17.4, 204, 24.2, 1540}};
+  const Coef& c = coef[E > 128 ? 2 : k >= 4 ? 1 : 0];
+  const double h = (double)H, tk = 1e-6 * (double)T * k, te = 1e-6 * (double)T * E, passes = (E + 127) / 128;
+  const long long big = 128 * 256;
+  const double tiles = T < big ? (double)((2 * T + big - 1) / big) * (c.t64 + c.t64h * h)
+                               : (double)((T + big - 1) / big) * (c.t128 + c.t128h * h);
+  const double floor = c.floor * h, chains = c.chain * tk * h;
+  const double h4 = H > 4096 ? 1e-3 * (h - 4096) : 0, h8 = H > 8192 ? 1e-3 * (h - 8192) : 0;
+  return c.c + c.ck * k + tiles * passes + (floor > chains ? floor : chains) + c.te * te + c.tk * tk +
+         h4 * (c.h4 + c.h4tk * tk) + h8 * (c.h8 + c.h8tk * tk);
+}
+
 bool gate_filtered(long long T, long long H, int E, int k) {
-  if (E <= 64) return false;
-  if (E <= 128) return k >= 4 ? (T - 8192) * H >= (12LL << 20) : T >= 32768 || T * H >= (1LL << 26);
-  return k <= 4 && T * E * H >= (k == 1 ? 1LL << 33 : 1LL << 34) / 100 * 95;
+  // (the chain list is indexed with 32 bits)
+  return E > 64 && T * E < (1LL << 31) && filter_us(T, H, E, k) < gate_us(T, H, E, k);
 }
 
 // the filter's kernels in order on `s`

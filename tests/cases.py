@@ -6,6 +6,7 @@ call is still the plain oracle on a slice of tokens.
 """
 from __future__ import annotations
 
+import ctypes
 import os
 from concurrent.futures import ThreadPoolExecutor
 from dataclasses import dataclass
@@ -15,6 +16,7 @@ import numpy as np
 import torch
 
 from oracle import oracle as O
+from paper_2609_21483_amd import build as BLD
 from paper_2609_21483_amd import workloads as W
 
 THREADS = max(1, min(16, os.cpu_count() or 1))
@@ -143,6 +145,13 @@ def rel_err(y_gpu: np.ndarray, y_ref: np.ndarray) -> float:
 
 def bf16_to_f64(t: torch.Tensor) -> np.ndarray:
     return t.float().cpu().numpy().astype(np.float64)
+
+
+def gate_filtered(T: int, H: int, E: int, k: int) -> bool:
+    """Whether the library routes this problem by its filter (moe::gate_filtered)."""
+    fn = ctypes.CDLL(BLD.LIB)._ZN3moe13gate_filteredExxii
+    fn.argtypes, fn.restype = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int, ctypes.c_int], ctypes.c_bool
+    return fn(T, H, E, k)
 
 
 # ---- the cost model on the oracle's tables (plan parity) -------------------

@@ -10,7 +10,7 @@ import torch
 
 from oracle import oracle as O
 from paper_2609_21483_amd import workloads as W
-from tests.cases import make_case
+from tests.cases import gate_filtered, make_case
 
 pytestmark = pytest.mark.gpu
 
@@ -250,8 +250,7 @@ GATES = [
     (31, 320, 65, 8, True), (1030, 128, 128, 3, False), (5000, 64, 126, 8, True),  # 128
     (300, 128, 129, 8, True), (1100, 64, 256, 1, False), (3000, 96 * 2, 200, 7, True),  # 256
     (67, 128, 257, 4, False), (1500, 64, 512, 8, True),                     # 512
-    (32768, 64, 66, 2, True), (16384, 1536, 72, 4, False),                  # the filter, one and four entries per token
-    (32768, 4096, 130, 1, False),                                           # the filter above 128 experts
+    (32768, 64, 66, 2, True), (16384, 1536, 72, 4, False), (32768, 4096, 130, 1, False),  # many tokens (two by the filter)
 ]
 
 
@@ -275,6 +274,19 @@ def test_gate_classes(B, T, H, E, k, bias):
     torch.cuda.synchronize()
     assert np.array_equal(idx.cpu().numpy(), idx_ref)
     assert np.max(np.abs(w.cpu().numpy() - w_ref)) <= 1e-6
+
+
+# one problem for each kernel of the filter: logit tiles of 64 and of 128
+# tokens, E <= 128 and above, and chains k < 4, k < 8, k = 8
+FILTER_GATES = [(8200, 832, 66, 1, False), (8300, 1088, 100, 6, True), (8200, 1216, 66, 8, True),
+                (33000, 512, 66, 1, True), (32800, 384, 66, 4, False), (33000, 448, 66, 8, False),
+                (4100, 1472, 257, 2, True), (8300, 2048, 300, 8, False), (41000, 1600, 129, 1, True)]
+
+
+@pytest.mark.parametrize("T,H,E,k,bias", FILTER_GATES)
+def test_gate_filter_classes(B, T, H, E, k, bias):
+    assert gate_filtered(T, H, E, k)
+    test_gate_classes(B, T, H, E, k, bias)
 
 
 def test_gate_masked_experts(B):
