@@ -244,8 +244,6 @@ void compute_layout(moe_handle* h) {
   L.plan = take(sizeof(moe_plan));
   L.err = take(sizeof(int32_t) * 4);
   h->off_calib = take(sizeof(DevCalib));
-  h->off_gate = take(h->filter ? bind_filter(nullptr, nullptr, T, c.hidden, c.n_experts)
-                     : c.n_experts % 4 ? sizeof(uint16_t) * (size_t)gate_ldw(c.n_experts) * c.hidden : 0);
   h->off_sched = take(sizeof(int32_t) * (size_t)KOPT * SCHED_WORDS + sizeof(StoredPlan));
   h->off_blk_cnt = take(sizeof(int32_t) * (size_t)h->nblk_cap * El);
   h->off_blk_off = take(sizeof(int32_t) * (size_t)h->nblk_cap * El);
@@ -255,6 +253,9 @@ void compute_layout(moe_handle* h) {
   h->off_done = take(sizeof(int32_t));
   h->off_ctl[0] = take(sizeof(int32_t) * (size_t)h->ctl_words);
   h->off_ctl[1] = take(sizeof(int32_t) * (size_t)h->ctl_words);
+  // the gate's scratch (past the control words, which moe_set_workspace clears)
+  h->off_gate = take(h->filter ? bind_filter(nullptr, nullptr, T, c.hidden, c.n_experts)
+                     : c.n_experts % 4 ? sizeof(uint16_t) * (size_t)gate_ldw(c.n_experts) * c.hidden : 0);
   h->arows = a_rows(c);
   h->orows = out_rows(c);
   L.A = take(sizeof(uint16_t) * h->arows * c.hidden);
