@@ -64,7 +64,7 @@ constexpr int GG = 16;
 constexpr int GTOK = NTH / GG;    // tokens per workgroup
 
 __device__ __forceinline__ bool better(float v, int e, float bv, int be) {
-  return v > bv || (v == bv && e < be);
+  return (v > bv) | ((v == bv) & (e < be));
 }
 __device__ __forceinline__ void group_argmax(float& v, int& e) {
 #pragma unroll
@@ -75,12 +75,29 @@ __device__ __forceinline__ void group_argmax(float& v, int& e) {
   }
 }
 
-// approximate logit of (g, e) with bias, and its half-width
-__device__ __forceinline__ void interval(const FilterArgs& a, int g, int e, float xn, float& l, float& d) {
-  l = a.lt[(size_t)g * a.E + e];
-  if (a.bias) l = l + a.bias[e];
-  d = a.bound * xn * a.wn[e];
+// The interval [lo, hi] that holds the defined logit: l is the approximate one
+// with bias, norms = ||x|| ||w||.  Neither end is NaN.  While the norms bound the
+// sum far from overflow, l is infinite or NaN exactly if the bias is, and so is
+// the defined logit (a masked expert: both ends -inf, so it is a candidate only
+// where fewer than k experts are left; NaN is never chosen); past that, or with
+// an infinite or NaN input, anything may come out.
+__device__ __forceinline__ void interval(float l, float norms, float bound, float& lo, float& hi) {
+  float d = bound * norms;
   d = d + 4.0f * 5.9604645e-8f * (fabsf(l) + d) + 1e-30f;
+  lo = l - d;
+  hi = l + d;
+  if (!(fabsf(l) < INFINITY)) lo = hi = l == l ? l : -INFINITY;
+  if (!(norms < 1e30f)) {
+    lo = -INFINITY;
+    hi = INFINITY;
+  }
+}
+
+// the interval of (g, e) from the logits in memory
+__device__ __forceinline__ void interval_at(const FilterArgs& a, int g, int e, float xn, float& lo, float& hi) {
+  float l = a.lt[(size_t)g * a.E + e];
+  if (a.bias) l = l + a.bias[e];
+  interval(l, xn * a.wn[e], a.bound, lo, hi);
 }
 
 // Candidates of the ntok tokens from g0 (one workgroup of NTH threads, GTOK
@@ -106,12 +123,7 @@ __device__ __forceinline__ void cand_tile(const FilterArgs& a, int g0, int ntok,
     for (int i = 0; i < EPL; ++i) {
       const int e = gl + GG * i;
       lo[i] = hi[i] = -INFINITY;
-      if (e < a.E) {
-        float l, d;
-        interval(a, gs, e, xn, l, d);
-        lo[i] = l - d;
-        hi[i] = l + d;
-      }
+      if (e < a.E) interval_at(a, gs, e, xn, lo[i], hi[i]);
     }
     float tau = -INFINITY;
     for (int r = 0; r < a.k; ++r) {
@@ -128,7 +140,7 @@ __device__ __forceinline__ void cand_tile(const FilterArgs& a, int g0, int ntok,
     }
     int mine = 0;
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) mine += valid && hi[i] >= tau;
+    for (int i = 0; i < EPL; ++i) mine += valid && gl + GG * i < a.E && hi[i] >= tau;
 #pragma unroll
     for (int d = GG / 2; d > 0; d >>= 1) mine += __shfl_xor(mine, d, WAVE);
     if (gl == 0) {
@@ -171,9 +183,9 @@ __device__ __forceinline__ void cand_tile(const FilterArgs& a, int g0, int ntok,
       const int e = gl + GG * i;
       bool c = false;
       if (valid && e < a.E) {
-        float l, d;
-        interval(a, gs, e, xn, l, d);
-        c = l + d >= tau;
+        float lo, hi;
+        interval_at(a, gs, e, xn, lo, hi);
+        c = hi >= tau;
       }
       const uint32_t gm = (uint32_t)(__ballot(c) >> (gw * GG)) & ((1u << GG) - 1);
       if (c) {
@@ -511,11 +523,9 @@ __global__ void __launch_bounds__(2 * NTH) gate_tile2_kernel(FilterArgs a) {
       const int e = q * EQ + i;
       up[i] = -INFINITY;
       if (e < a.E) {
-        const float l = tile[tq * G2_PAD + e];
-        float d = a.bound * xn * wn_s[e];
-        d = d + 4.0f * 5.9604645e-8f * (fabsf(l) + d) + 1e-30f;
-        insert(l - d);
-        up[i] = l + d;
+        float lo;
+        interval(tile[tq * G2_PAD + e], xn * wn_s[e], a.bound, lo, up[i]);
+        insert(lo);
       }
     }
   }
@@ -857,14 +867,15 @@ __global__ void __launch_bounds__(NTH) gate_final_kernel(FilterArgs a) {
         int e = ce[i];
 #pragma unroll
         for (int j = 0; j < MAX_TOPK; ++j) {
-          if (better(v, e, tv[j], ti[j])) {
-            const float ov = tv[j];
-            const int oe = ti[j];
-            tv[j] = v;
-            ti[j] = e;
-            v = ov;
-            e = oe;
-          }
+          // (selects: as a branch, gfx950 code of this compiler kept the
+          // old id where the values are equal)
+          const bool b = better(v, e, tv[j], ti[j]);
+          const float ov = tv[j];
+          const int oe = ti[j];
+          tv[j] = b ? v : ov;
+          ti[j] = b ? e : oe;
+          v = b ? ov : v;
+          e = b ? oe : e;
         }
       }
     }

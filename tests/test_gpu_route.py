@@ -316,3 +316,81 @@ def test_gate_masked_experts(B):
     torch.cuda.synchronize()
     got = idx.cpu().numpy()
     assert not np.any(got == 3) and got.min() >= 0 and got.max() < E
+
+
+@pytest.mark.parametrize("T,H,E,k", [
+    (100, 832, 66, 4), (300, 320, 257, 3),                            # the gate that evaluates every logit
+    (8200, 960, 66, 3), (8300, 1088, 100, 6), (8200, 1216, 66, 8),    # the filter, E <= 128
+    (4100, 1472, 257, 2), (8300, 2048, 300, 8),                       # the filter above 128 experts
+])
+def test_gate_infinities_and_nans(B, T, H, E, k):
+    """Masked experts (bias -inf or the lowest float), too few of them left,
+    biases of +inf and NaN, and tokens with infinite, NaN, huge and zero values:
+    the ids of the defined logits from either gate, ties to the smaller id, NaN
+    never chosen (no id left: 1 << 30)."""
+    from tests.cases import oracle_logits
+    assert gate_filtered(T, H, E, k) == (T > 4000)
+    rng = torch.Generator().manual_seed(T + E)
+    x = torch.randn(T, H, generator=rng).to(torch.bfloat16)
+    wg = (0.05 * torch.randn(H, E, generator=rng)).to(torch.bfloat16)
+    x[3, 5] = float("inf")
+    x[4, 7] = float("-inf")
+    x[5, 0] = float("nan")
+    x[6] *= 1e30
+    x[7] *= 3e37
+    x[8] = 0
+    base = oracle_logits(W.as_u16_numpy(x), W.as_u16_numpy(wg), None)
+    inf, low = float("inf"), torch.finfo(torch.float32).min
+    left, cut = torch.arange(E) % (E // (k + 2)) == 1, torch.arange(E) >= max(k - 2, 1)
+    biases = {"none": None, "masked": torch.where(left, 0.0, -inf), "lowest": torch.where(left, 0.0, low),
+              "few": torch.where(cut, -inf, 0.0), "few_lowest": torch.where(cut, low, 0.0),
+              "plus": torch.where(torch.arange(E) == E - 2, inf, 0.0),
+              "nan": torch.where(torch.arange(E) % 3 == 0, float("nan"), 0.0)}
+    xd, wd = x.cuda(), wg.cuda()
+    for name, b in biases.items():
+        with np.errstate(invalid="ignore", over="ignore"):
+            lg = (base if b is None else base + b.numpy()).astype(np.float64)
+        nan = np.isnan(lg)
+        order = np.lexsort((np.broadcast_to(np.arange(E), lg.shape), -np.where(nan, -inf, lg), nan), axis=1)[:, :k]
+        ref = np.where(np.take_along_axis(nan, order, 1), 1 << 30, order)
+        idx = torch.full((T, k), -7, dtype=torch.int32, device="cuda")
+        w = torch.zeros((T, k), device="cuda")
+        B.moe_route_topk_static(T, H, E, k, xd, wd, None if b is None else b.cuda(), idx, w)
+        torch.cuda.synchronize()
+        bad = np.nonzero((idx.cpu().numpy() != ref).any(axis=1))[0]
+        assert bad.size == 0, (name, bad[:5], idx[bad[0]].tolist(), ref[bad[0]], lg[bad[0]][ref[bad[0]] % E])
+        if name in ("masked", "few", "lowest", "few_lowest"):
+            rows, top = slice(9, None), np.take_along_axis(lg, order, 1)[9:]
+            p = np.exp(top - top[:, :1])
+            assert np.max(np.abs(w.cpu().numpy()[rows] - p / p.sum(1, keepdims=True))) <= 1e-6, name
+
+
+@pytest.mark.parametrize("R,Tr,H,E", [(1, 1200, 128, 64), (2, 4150, 1216, 66)])  # the gate; the filter
+def test_tokens_without_valid_ids_are_flagged(B, R, Tr, H, E):
+    """Tokens whose logits are all NaN get no valid id: moe_route reports and
+    counts them, and the other tokens' tables are intact (the gate's own count
+    blocks, more than one workgroup of the table builder)."""
+    k, El = 8, 8
+    shape = W.MoeShape("nan_rows", 97, R, Tr, H, 64, E, k, El)
+    T = shape.T
+    assert gate_filtered(T, H, E, k) == (T > 4000)
+    rng = torch.Generator().manual_seed(5)
+    x = torch.randn(T, H, generator=rng).to(torch.bfloat16)
+    wg = (0.05 * torch.randn(H, E, generator=rng)).to(torch.bfloat16)
+    rows = [0, 511, 512, T - 1]
+    x[rows, 1] = float("nan")
+    hd = Handle(B, shape)
+    try:
+        idx = torch.full((T, k), -7, dtype=torch.int32, device="cuda")
+        w = torch.zeros((T, k), device="cuda")
+        B.moe_route(hd.h, x.cuda(), wg.cuda(), None, k, idx, w)
+        assert B.moe_sync_status(hd.h) == B.MOE_ERR_ROUTING
+        got = idx.cpu().numpy()
+        assert np.all(got[rows] == 1 << 30)
+        tab = O.route_tables(got, R, Tr, 0, El)
+        assert np.array_equal(hd.view("slot", T * k).reshape(T, k), tab.slot)
+        assert np.array_equal(hd.view("off", El + 1), tab.off)
+        assert hd.view("stats", 16)[5] == len(rows)
+        assert B.moe_sync_status(hd.h) == B.MOE_OK
+    finally:
+        hd.close()
