@@ -271,8 +271,11 @@ moe_status moe_pack_weights(moe_handle* h, const uint16_t* w1, const uint16_t* w
  * in fp32 over ascending h (one accumulator per (token, expert)); the top_k
  * largest logits are selected (ties -> smaller expert id), written in
  * descending order to topk_idx int32 [T][k]; topk_w fp32 [T][k] receives the
- * selected softmax probabilities divided by their sum.  top_k must equal the
- * configured k. */
+ * selected softmax probabilities divided by their sum.  A NaN logit is never
+ * selected; a token with fewer than k others gets id 2^30 for the rest, which
+ * latches MOE_ERR_ROUTING.  top_k must equal the configured k.  x and wg may
+ * start at any bf16 value; off a 16-byte boundary they are copied first (x
+ * into the workspace's A). */
 moe_status moe_route(moe_handle* h, const uint16_t* x, const uint16_t* wg,
                      const float* logit_bias, int32_t top_k, int32_t* topk_idx,
                      float* topk_w, void* stream);
@@ -287,7 +290,8 @@ moe_status moe_route(moe_handle* h, const uint16_t* x, const uint16_t* wg,
  * forbid allocation.  It builds no routing tables (moe_build_tables does).
  * x: bf16 [T][H], wg: bf16 [H][E], logit_bias: fp32 [E] or NULL; writes
  * topk_idx int32 [T][top_k] and topk_w fp32 [T][top_k] as moe_route does.
- * The gate's scratch (a padded copy of wg; for large batches of more than 64
+ * The gate's scratch (a copy of wg where E is no multiple of 4, and of wg or
+ * x where they start off a 16-byte boundary; for large batches of more than 64
  * experts, intermediate logits, norms and candidate chains) lives in a static
  * device array of MOE_ROUTE_STATIC_SCRATCH_BYTES that each GPU the library
  * runs on holds until the process ends; problems of more than about
@@ -309,7 +313,8 @@ moe_status moe_route_topk_static(int32_t T, int32_t H, int32_t E, int32_t top_k,
 moe_status moe_build_tables(moe_handle* h, const int32_t* topk_idx, void* stream);
 
 /* The MoE layer (section 2.1 stages 1-5) on the tables built from topk_idx.
- * x: bf16 [T][H] staging regions; topk_idx/topk_w: the routing result
+ * x: bf16 [T][H] staging regions (16-byte aligned where the layer has shared
+ * experts); topk_idx/topk_w: the routing result
  * (topk_idx must be the array the current tables were built from: checked by
  * address); packed: from moe_pack_weights; y: bf16 [T][H] output staging
  * regions, y[g] = sum over local j of topk_w[g,j] * FFN(x[g]) (+ the shared

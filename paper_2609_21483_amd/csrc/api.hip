@@ -255,7 +255,7 @@ void compute_layout(moe_handle* h) {
   h->off_ctl[1] = take(sizeof(int32_t) * (size_t)h->ctl_words);
   // the gate's scratch (past the control words, which moe_set_workspace clears)
   h->off_gate = take(h->filter ? bind_filter(nullptr, nullptr, T, c.hidden, c.n_experts)
-                     : c.n_experts % 4 ? sizeof(uint16_t) * (size_t)gate_ldw(c.n_experts) * c.hidden : 0);
+                               : sizeof(uint16_t) * (size_t)gate_ldw(c.n_experts) * c.hidden);
   h->arows = a_rows(c);
   h->orows = out_rows(c);
   L.A = take(sizeof(uint16_t) * h->arows * c.hidden);
@@ -394,7 +394,8 @@ FwdArgs fwd_args(moe_handle* h, const uint16_t* x, const int32_t* topk_idx, cons
   a.nt0 = h->nt0;
   a.nt1 = h->few ? (h->cfg.hidden + THIN_N - 1) / THIN_N : h->nt1;
   a.nsplit = h->nsplit;
-  a.gather = h->few && mode != MOE_MODE_SERIAL;  // (a separate GEMM0 reads what the dispatch stage wrote)
+  // (a separate GEMM0 reads what the dispatch stage wrote; gathered rows are loaded 16 bytes at a time, aligned)
+  a.gather = h->few && mode != MOE_MODE_SERIAL && dma_aligned(x);
   move_units(h, &a.dt, &a.ct);
   a.mt_max = h->mt_max;
   a.ctl_words = h->ctl_words;
@@ -695,6 +696,10 @@ moe_status moe_route(moe_handle* h, const uint16_t* x, const uint16_t* wg, const
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   FilterArgs g{};
   g.x = x;
+  if (!dma_aligned(x)) {  // into A, which holds at least T rows and nothing that outlives the old tables
+    launch_copy_rows(x, at<uint16_t>(h, h->lay.A), (long long)h->T * h->cfg.hidden, s);
+    g.x = at<uint16_t>(h, h->lay.A);
+  }
   g.wg = wg;
   g.bias = logit_bias;
   g.topk_idx = topk_idx;
@@ -928,12 +933,25 @@ moe_status moe_route_topk_static(int32_t T, int32_t H, int32_t E, int32_t top_k,
   g.k = top_k;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   char* base = nullptr;
-  const bool filter = gate_filtered(T, H, E, top_k);
-  if (filter || E % 4) {
+  const bool aligned = dma_aligned(x), filter = aligned && gate_filtered(T, H, E, top_k);
+  if (filter || !aligned || gate_padded(wg, E)) {
     moe_status st = static_scratch(&base);
     if (st != MOE_OK) return st;
   }
-  if (filter) {
+  if (!aligned) {
+    // the scratch holds the gate's copy and as many token rows as fit behind it
+    const size_t off = align_up(sizeof(uint16_t) * (size_t)gate_ldw(E) * H, 256);
+    uint16_t* rows = reinterpret_cast<uint16_t*>(base + off);
+    const int step = (int)std::min<size_t>((size_t)T, (MOE_ROUTE_STATIC_SCRATCH_BYTES - off) / (sizeof(uint16_t) * (size_t)H));
+    for (int t = 0; t < T; t += step) {
+      g.T = std::min(step, T - t);
+      g.x = rows;
+      g.topk_idx = topk_idx + (size_t)t * top_k;
+      g.topk_w = topk_w + (size_t)t * top_k;
+      launch_copy_rows(x + (size_t)t * H, rows, (long long)g.T * H, s);
+      launch_gate(g, gate_geometry(g.T, E), reinterpret_cast<uint16_t*>(base), s);
+    }
+  } else if (filter) {
     bind_filter(&g, base, T, H, E);
     launch_gate_filter(g, s);
   } else {

@@ -332,7 +332,7 @@ __global__ void __launch_bounds__((GateGeo<EC, LM, TWV>::NW * WAVE)) gate_kernel
 }
 
 // A copy of the gate [H][E] with rows of E4 values (E rounded up to a multiple
-// of 4).  In front of the gate it takes 3 to 5 us; reading unpadded rows value
+// of 4), aligned.  In front of the gate it takes 3 to 5 us; reading unpadded rows value
 // by value instead made the gate 40% slower (E = 127 against 128, H = 4096).
 __global__ void __launch_bounds__(NTH) gate_pad_kernel(const uint16_t* wg, uint16_t* out, int H, int E, int E4) {
   const int n = H * E4;
@@ -340,6 +340,17 @@ __global__ void __launch_bounds__(NTH) gate_pad_kernel(const uint16_t* wg, uint1
     const int h = i / E4, e = i - h * E4;
     out[i] = e < E ? wg[(size_t)h * E + e] : (uint16_t)0;
   }
+}
+
+// A copy of token rows at an aligned address, where the caller's is not (a view
+// into a larger buffer): value by value.
+__global__ void __launch_bounds__(NTH) copy_rows_kernel(const uint16_t* src, uint16_t* dst, long long n) {
+  for (long long i = (long long)blockIdx.x * NTH + threadIdx.x; i < n; i += (long long)gridDim.x * NTH) dst[i] = src[i];
+}
+
+void launch_copy_rows(const uint16_t* src, uint16_t* dst, long long n, hipStream_t s) {
+  const long long grid = (n + 4 * NTH - 1) / (4 * NTH);
+  copy_rows_kernel<<<(int)(grid < 16384 ? grid : 16384), NTH, 0, s>>>(src, dst, n);
 }
 
 // Every (expert class, shape, token wavefronts) with a kernel; the most token
@@ -381,7 +392,7 @@ GateGeometry gate_geometry(int T, int E) {
 void launch_gate(const GateArgs& args, const GateGeometry& g, uint16_t* pad, hipStream_t s) {
   GateArgs a = args;
   a.ldw = gate_ldw(a.E);
-  if (a.ldw != a.E) {
+  if (gate_padded(a.wg, a.E)) {
     const int n = a.H * a.ldw, grid = (n + 4 * NTH - 1) / (4 * NTH);
     gate_pad_kernel<<<grid, NTH, 0, s>>>(a.wg, pad, a.H, a.E, a.ldw);
     a.wg = pad;

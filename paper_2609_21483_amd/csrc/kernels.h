@@ -47,10 +47,17 @@ struct GateGeometry {
 constexpr int GATE_SIMDS = 1024;  // SIMDs of gfx950
 GateGeometry gate_geometry(int T, int E);
 bool gate_filtered(long long T, long long H, int E, int k);  // the filtering gate is the faster one
-// pad: device memory for the padded gate, H * gate_ldw(E) values (unused when
-// E is a multiple of 4)
+// pad: device memory for a copy of the gate, H * gate_ldw(E) values (unused
+// when !gate_padded).  x is 16-byte aligned.
 void launch_gate(const GateArgs& a, const GateGeometry& g, uint16_t* pad, hipStream_t s);
 constexpr int gate_ldw(int E) { return (E + 3) / 4 * 4; }
+// The operands are loaded 16 bytes at a time, aligned: the gate kernel reads a
+// copy of wg unless its rows and its address allow that, and both gates one of
+// x (launch_copy_rows) unless its address does.
+inline bool dma_aligned(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+inline bool gate_padded(const uint16_t* wg, int E) { return gate_ldw(E) != E || !dma_aligned(wg); }
+// n values (a multiple of 64) from a pointer aligned to one value
+void launch_copy_rows(const uint16_t* src, uint16_t* dst, long long n, hipStream_t s);
 
 struct TableArgs {
   const int32_t* topk_idx;

@@ -215,6 +215,38 @@ def test_few_rows_under_skewed_routing(B, shape, spread, split):
         layer.close()
 
 
+@pytest.mark.parametrize("shape", [W.MoeShape("view_few", 76, 2, 40, 192, 192, 16, 2, 4),
+                                   W.MoeShape("view_few_wide", 75, 1, 64, 128, 512, 48, 8, 40),
+                                   W.MoeShape("view_general", 74, 2, 300, 128, 192, 4, 2, 2)], ids=lambda s: s.name)
+@pytest.mark.parametrize("off", [1, 4])
+def test_tokens_off_a_16_byte_boundary(B, shape, off):
+    """x as a view that starts anywhere in a larger buffer: y has the bits of
+    its aligned copy's, in layers that gather their rows from x too."""
+    c = make_case(shape.with_(w_std=0.05))
+    idx, w = W.random_routing(shape.T, shape.n_experts, shape.top_k, seed=3)
+    ml = B.MoeLayer(shape, c.w1, c.w3, c.w2)
+    try:
+        x = c.x.cuda()
+        buf = torch.zeros(x.numel() + off, dtype=torch.bfloat16, device="cuda")
+        view = buf[off:].view(x.shape)
+        view.copy_(x)
+        idx_d, w_d = torch.from_numpy(idx.astype(np.int32)).cuda(), torch.from_numpy(w.astype(np.float32)).cuda()
+        B.moe_build_tables(ml.h, idx_d)
+        ys = []
+        for xv, mode in ((x, "dynamic"), (view, "dynamic"), (view, "static"), (view, "serial")):
+            y = torch.full((shape.T, shape.hidden), float("nan"), dtype=torch.bfloat16, device="cuda")
+            ml.forward(xv, idx_d, w_d, y, mode)
+            assert B.moe_sync_status(ml.h) == B.MOE_OK
+            ys.append(y)
+        y = torch.empty_like(ys[0])
+        B.moe_forward_stack([ml.h], view, [idx_d], [w_d], [ml.packed], [y])
+        assert B.moe_sync_status(ml.h) == B.MOE_OK
+        for o in ys[1:] + [y]:
+            assert torch.equal(o.view(torch.int16), ys[0].view(torch.int16))
+    finally:
+        ml.close()
+
+
 def test_no_local_pairs(B):
     """Every token routed off this GPU: y must be all zeros (no shared experts),
     or only the shared output on rank 0."""

@@ -394,3 +394,42 @@ def test_tokens_without_valid_ids_are_flagged(B, R, Tr, H, E):
         assert B.moe_sync_status(hd.h) == B.MOE_OK
     finally:
         hd.close()
+
+
+def _view_at(t, off):
+    """t's values in a contiguous view that starts off values into a buffer."""
+    buf = torch.zeros(t.numel() + off, dtype=t.dtype, device="cuda")
+    v = buf[off:].view(t.shape)
+    v.copy_(t)
+    assert v.is_contiguous() and v.data_ptr() % 16 == 2 * off % 16
+    return v
+
+
+@pytest.mark.parametrize("xo,wo", [(0, 1), (0, 4), (1, 0), (4, 3)])
+@pytest.mark.parametrize("T,H,E,k", [
+    (65, 192, 8, 2), (300, 64, 128, 8), (70, 128, 30, 4),   # rows of a multiple of 4 values, and not
+    (8200, 960, 66, 4),                                     # the filter
+    (8000, 8192, 8, 2),                                     # more rows than the static scratch holds
+])
+def test_operands_off_a_16_byte_boundary(B, T, H, E, k, xo, wo):
+    """Views that start anywhere in a larger buffer are routed as their aligned
+    copies are, by both entry points."""
+    rng = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn(T, H, device="cuda", generator=rng).to(torch.bfloat16)
+    wg = (0.05 * torch.randn(H, E, device="cuda", generator=rng)).to(torch.bfloat16)
+    shape = W.MoeShape("views", 96, 1, T, H, 64, E, k, min(4, E))
+    hd = Handle(B, shape)
+    try:
+        out = []
+        for xv, wv in ((x, wg), (_view_at(x, xo), _view_at(wg, wo))):
+            for route in (lambda *a: B.moe_route(hd.h, xv, wv, None, k, *a),
+                          lambda *a: B.moe_route_topk_static(T, H, E, k, xv, wv, None, *a)):
+                idx = torch.full((T, k), -7, dtype=torch.int32, device="cuda")
+                w = torch.zeros((T, k), device="cuda")
+                route(idx, w)
+                assert B.moe_sync_status(hd.h) == B.MOE_OK
+                out.append((idx, w))
+        for idx, w in out[1:]:
+            assert torch.equal(idx, out[0][0]) and torch.equal(w, out[0][1])
+    finally:
+        hd.close()
