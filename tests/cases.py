@@ -154,6 +154,17 @@ def gate_filtered(T: int, H: int, E: int, k: int) -> bool:
     return fn(T, H, E, k)
 
 
+def gate_kernel_of(T: int, E: int):
+    """(expert class, large shape, token wavefronts) of the one-kernel gate (moe::gate_geometry)."""
+    class Geometry(ctypes.Structure):
+        _fields_ = [(f, ctypes.c_int) for f in ("ec", "large", "tw", "tt", "grid")]
+
+    fn = ctypes.CDLL(BLD.LIB)._ZN3moe13gate_geometryEii
+    fn.argtypes, fn.restype = [ctypes.c_int, ctypes.c_int], Geometry
+    g = fn(T, E)
+    return g.ec, bool(g.large), g.tw
+
+
 # ---- the cost model on the oracle's tables (plan parity) -------------------
 
 def oracle_tiles(B, h, shape, tab, K):

@@ -2,9 +2,13 @@
 every logit, or the certified filter), against measured times of both on an
 MI355X: the faster one at each of these sizes, where they differ by a tenth or
 more."""
+import os
+import re
+
 import pytest
 
-from tests.cases import gate_filtered
+from paper_2609_21483_amd import build as BLD
+from tests.cases import gate_filtered, gate_kernel_of
 
 # (T, H, E, k): us of the one-kernel gate, of the filter; sizes at, just above
 # and between the steps of the gate's time (whole rounds of workgroups)
@@ -32,3 +36,13 @@ def test_the_faster_gate_is_picked(case, gate, filt):
 def test_the_filter_stays_within_its_indexes():
     assert not gate_filtered(1 << 22, 64, 512, 1)  # 2^31 chains at most
     assert not gate_filtered(1 << 22, 16384, 64, 1)
+
+
+def test_the_gpu_cases_reach_every_gate_kernel():
+    from tests.test_gpu_route import GATES
+    with open(os.path.join(BLD.CSRC, "gate.hip"), encoding="utf-8") as f:
+        src = f.read()
+    listed = src[src.index("#define MOE_GATE_CLASSES"):src.index("GateGeometry gate_geometry")]
+    kernels = {(int(ec), lm == "true", int(tw)) for ec, lm, tw in re.findall(r"X\((\d+), (true|false), (\d+)\)", listed)}
+    assert len(kernels) == 20
+    assert {gate_kernel_of(T, E) for T, H, E, k, _ in GATES if not gate_filtered(T, H, E, k)} == kernels

@@ -10,7 +10,7 @@ import torch
 
 from oracle import oracle as O
 from paper_2609_21483_amd import workloads as W
-from tests.cases import gate_filtered, make_case
+from tests.cases import gate_filtered, make_case, oracle_logits
 
 pytestmark = pytest.mark.gpu
 
@@ -128,11 +128,13 @@ def test_route_layers_on_several_streams(B):
 
 
 @pytest.mark.parametrize("bias", [False, True])
-def test_route_ties_and_candidate_overflow(B, bias):
-    """Exact ties and the exact fallback: zero token rows tie every expert
-    (more candidates than the per-token list holds), duplicated gate columns
-    tie expert pairs; equal logits go to the smaller id."""
-    shape = W.MoeShape("ties", 98, 2, 40, 128, 64, 128, 8, 8)
+@pytest.mark.parametrize("Tr,H", [(40, 128), (4100, 1216)], ids=["gate", "filter"])
+def test_route_ties_and_candidate_overflow(B, Tr, H, bias):
+    """Exact ties on either gate: zero token rows tie every expert (all of them
+    are the filter's candidates), duplicated gate columns tie expert pairs;
+    equal logits go to the smaller id."""
+    shape = W.MoeShape("ties", 98, 2, Tr, H, 64, 128, 8, 8)
+    assert gate_filtered(shape.T, H, 128, 8) == (Tr == 4100)
     rng = np.random.default_rng(11)
     x = torch.from_numpy(rng.standard_normal((shape.T, shape.hidden)).astype(np.float32)).to(torch.bfloat16)
     x[[0, 7, 41]] = 0
@@ -142,7 +144,7 @@ def test_route_ties_and_candidate_overflow(B, bias):
     wg[:, 100] = wg[:, 99]
     b = torch.from_numpy((-0.1 * np.log(np.arange(1, shape.n_experts + 1))).astype(np.float32)) if bias else None
     bu = None if b is None else b.numpy()
-    lg = O.gate_logits(W.as_u16_numpy(x), W.as_u16_numpy(wg), bu)
+    lg = oracle_logits(W.as_u16_numpy(x), W.as_u16_numpy(wg), bu)
     idx_ref, w_ref = O.softmax_topk(lg, shape.top_k)
     hd = Handle(B, shape)
     try:
@@ -163,8 +165,8 @@ def test_route_ties_and_candidate_overflow(B, bias):
     (1, 1, 8, 2, 8, 0.0),        # a single token
     (2, 300, 16, 4, 16, 0.0),    # every expert local
     (4, 77, 32, 8, 5, 2.5),      # heavy skew: empty local experts
-    (2, 513, 64, 6, 16, 1.0),    # more than one table block
-    (4, 10000, 8, 8, 8, 0.0),    # 320000 pairs: the lower-bound search samples every 128th slot
+    (2, 513, 64, 6, 16, 1.0),    # three table workgroups, the last of 2 tokens
+    (4, 10000, 8, 8, 8, 0.0),    # 320000 pairs: every token has every expert
 ])
 def test_build_tables_supplied_routing(B, R, Tr, E, k, El, skew):
     shape = W.MoeShape("t", 99, R, Tr, 64, 64, E, k, El)
@@ -179,7 +181,8 @@ def test_build_tables_supplied_routing(B, R, Tr, E, k, El, skew):
         hd.close()
 
 
-@pytest.mark.parametrize("Tr,rows", [(40, (5, 9, 11)), (300, (5, 290, 580))])  # one table block; three
+# one table workgroup, of 512 and of 960 tokens; four of them, whose bad ids the counting step adds up
+@pytest.mark.parametrize("Tr,rows", [(40, (5, 9, 11)), (300, (5, 290, 580)), (800, (5, 700, 1599))])
 def test_bad_routing_ids_are_flagged(B, Tr, rows):
     shape = W.MoeShape("t", 99, 2, Tr, 64, 64, 8, 2, 4)
     idx_ref, _ = W.random_routing(shape.T, 8, 2, seed=3)
@@ -206,10 +209,14 @@ def test_bad_routing_ids_are_flagged(B, Tr, rows):
 
 
 @pytest.mark.parametrize("R,Tr,E,k,El,S", [
-    (1, 256, 16, 2, 8, 1),       # one workgroup of 256 tokens, full
-    (1, 257, 16, 2, 8, 0),       # the first size of the 1024-token workgroup
-    (4, 256, 128, 8, 64, 2),     # its last
-    (5, 205, 128, 8, 64, 0),     # 1025 tokens: several workgroups, the second nearly empty
+    (1, 256, 16, 2, 8, 1),       # the 512-token workgroup, half full
+    (1, 257, 16, 2, 8, 0),       # a wavefront with one token
+    (2, 256, 16, 2, 8, 1),       # full
+    (3, 171, 16, 2, 8, 0),       # 513 tokens: the first size of the 960-token workgroup
+    (4, 240, 128, 8, 64, 2),     # its last
+    (31, 31, 128, 8, 64, 0),     # 961 tokens: the first size of several workgroups
+    (4, 256, 128, 8, 64, 2),     # two full ones
+    (5, 205, 128, 8, 64, 0),     # 1025 tokens: the last of three has one
     (2, 2048, 64, 8, 1, 0),      # one local expert
     (64, 1040, 64, 1, 64, 0),    # more count words than the table blocks sum themselves; 64 ranks
 ])
@@ -250,6 +257,8 @@ GATES = [
     (31, 320, 65, 8, True), (1030, 128, 128, 3, False), (5000, 64, 126, 8, True),  # 128
     (300, 128, 129, 8, True), (1100, 64, 256, 1, False), (3000, 96 * 2, 200, 7, True),  # 256
     (67, 128, 257, 4, False), (1500, 64, 512, 8, True),                     # 512
+    # the classes up to 64 experts with one token wavefront a workgroup or with several, and 16 in the large shape
+    (5000, 128, 8, 2, True), (100, 128, 12, 3, False), (33000, 64, 16, 4, True), (500, 128, 24, 4, True), (300, 128, 48, 6, False),
     (32768, 64, 66, 2, True), (16384, 1536, 72, 4, False), (32768, 4096, 130, 1, False),  # many tokens (two by the filter)
 ]
 
@@ -265,7 +274,6 @@ def test_gate_classes(B, T, H, E, k, bias):
     if E > 2:
         wg[:, E - 1] = wg[:, 1]
     b = torch.randn(E, generator=rng) if bias else None
-    from tests.cases import oracle_logits
     lg = oracle_logits(W.as_u16_numpy(x), W.as_u16_numpy(wg), None if b is None else b.numpy())
     idx_ref, w_ref = O.softmax_topk(lg, k)
     idx = torch.full((T, k), -7, dtype=torch.int32, device="cuda")
@@ -328,7 +336,6 @@ def test_gate_infinities_and_nans(B, T, H, E, k):
     biases of +inf and NaN, and tokens with infinite, NaN, huge and zero values:
     the ids of the defined logits from either gate, ties to the smaller id, NaN
     never chosen (no id left: 1 << 30)."""
-    from tests.cases import oracle_logits
     assert gate_filtered(T, H, E, k) == (T > 4000)
     rng = torch.Generator().manual_seed(T + E)
     x = torch.randn(T, H, generator=rng).to(torch.bfloat16)
