@@ -539,9 +539,9 @@ __device__ __forceinline__ TileRef decode_tile(const FwdArgs& a, const Sched& S,
   const int at = lane < ns ? nsx * (S.mb[s0 + lane] - S.mb[s0]) : 1 << 30;
   const int sl = __builtin_popcountll(__builtin_amdgcn_ballot_w64(at <= i)) - 1;
   i -= __builtin_amdgcn_readlane(at, sl);
-  const int seg = (L == 0 ? a.El : 0) + sl, rows = S.rows[s0 + sl], c = (rows + BM - 1) / BM, lo = 0;
+  const int seg = (L == 0 ? a.El : 0) + sl, rows = S.rows[s0 + sl], c = (rows + BM - 1) / BM;
   r.seg = seg;
-  r.mt = lo + i % c;
+  r.mt = i % c;
   const int slab = x + NXCD * (i / c);
   if (r.ph == 0) {
     r.nt = slab;

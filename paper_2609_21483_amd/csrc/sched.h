@@ -16,30 +16,13 @@ namespace moe {
 __device__ __forceinline__ int class_slabs(int ns, int x) { return ns > x ? (ns - x + NXCD - 1) / NXCD : 0; }
 
 // Readiness levels order the row tiles of a stage by when their inputs can be
-// complete.  Dispatch writes a local expert's rows in token order, so row
-// tile mt of a segment of `rows` rows is complete once the fraction
-// min((mt + 1) * BM, rows) / rows of the segment is written; its level is
-// that fraction rounded up to a multiple of 1/NLVL (1..NLVL).  Shared-expert
-// rows are read straight from x: level 0, ready at launch.  With every
-// worker copying rows at the start, the routed row tiles all complete at
-// nearly the same time, and one routed level (NLVL = 1) measures fastest:
-// it keeps the row tiles of one expert and weight slab together, so the
-// tiles running on an XCD share that slab in its L2 (finer levels spread the
-// first claims over every expert and slab and fetch the weights several
-// times over).
-__device__ __forceinline__ int tiles_upto(int rows, int L) {  // routed tiles at level <= L
-  const int nmt = (rows + BM - 1) / BM;
-  if (L <= 0) return 0;
-  if (L >= NLVL) return nmt;
-  return min(nmt, (int)(((long long)L * rows) / ((long long)NLVL * BM)));
-}
-__device__ __forceinline__ int level_lo(int rows, bool shared, int L) {  // first row tile of level L
-  return shared ? 0 : tiles_upto(rows, L - 1);
-}
-__device__ __forceinline__ int level_tiles(int rows, bool shared, int L) {
-  if (shared) return L == 0 ? (rows + BM - 1) / BM : 0;
-  return tiles_upto(rows, L) - tiles_upto(rows, L - 1);
-}
+// complete.  Shared-expert rows are read straight from x: level 0, ready at
+// launch.  With every worker copying rows at the start, the routed row tiles
+// all complete at nearly the same time, and one routed level (NLVL = 1)
+// measures fastest: it keeps the row tiles of one expert and weight slab
+// together, so the tiles running on an XCD share that slab in its L2 (levels
+// by the fraction of a segment that must be written spread the first claims
+// over every expert and slab and fetch the weights several times over).
 
 // Queue order of the stages (chunk, phase) of a K-chunk schedule, skewed by
 // one chunk: (0,G0), (1,G0), (0,G1), (2,G0), (1,G1), ..., (K-1,G0), (K-2,G1),
