@@ -39,10 +39,11 @@ if ROOT not in sys.path:
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 METRIC = "MoE-layer µs + tokens/s at 1 GPU; HBM GB/s & MFMA util vs peak"
-# sources of the megakernel: a traffic figure measured on other sources is stale
+# sources of the megakernel and of the schedule it runs (the table builder stores it): a traffic figure measured on
+# other sources is stale
 KERNEL_SOURCES = ("paper_2609_21483_amd/csrc/forward.hip", "paper_2609_21483_amd/csrc/gemm.h",
                   "paper_2609_21483_amd/csrc/common.h", "paper_2609_21483_amd/csrc/kernels.h",
-                  "paper_2609_21483_amd/csrc/sched.h")
+                  "paper_2609_21483_amd/csrc/sched.h", "paper_2609_21483_amd/csrc/route.hip")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "megakernel_traffic.json")
 TOL = 2e-2  # max|y - y_ref| <= TOL * max|y_ref| over the checked rows
 
@@ -521,7 +522,8 @@ def measure_stack(B, stack, args, stream, flush, trace: bool):
         rec = {"layer": stack.ids[i], "plan": {"c": p.c, "K": p.K, "n_steal": p.n_steal, "final_all": p.final_all,
                                                 "t_pred_us": p.t_pred_s * 1e6},
                "local_pairs": int(stats[i][0]), "gflop": flops[i] / 1e9,
-               "route_exact_chains": int(stats[i][8]),
+               # experts whose logits the filtering gate evaluated; T * top_k where the gate evaluates every logit
+               "route_candidates": int(stats[i][8]),
                "layer_us": float(np.median(dyn)),
                "layer_us_p10_p90": [float(np.percentile(dyn, 10)), float(np.percentile(dyn, 90))],
                "layer_us_flushed": float(np.median(fl[i])) if fl else None,

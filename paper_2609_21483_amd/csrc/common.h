@@ -88,7 +88,7 @@ constexpr int TRACE_HDR = 64;            // header bytes; per-segment counts fol
 
 // stats words written by the table builder
 constexpr int ST_X = 0, ST_XLOCAL = 1, ST_XIN = 2, ST_ULOCAL = 3, ST_UIN = 4, ST_BADIDS = 5;
-// written by the gate: candidates whose defined logit was evaluated (all tokens)
+// written by the gate: the filter's candidates (all tokens), T * k where every logit is evaluated
 constexpr int ST_CANDS = 8;
 // written by the table builder: GEMM tiles of the layer at each stored chunk
 // option (KOPT words; the cost model's tile counts, Eq 14)
