@@ -339,7 +339,7 @@ __global__ void __launch_bounds__(NTH) gate_tile_kernel(FilterArgs a) {
   cand_tile<EPL>(a, g0, GT_M, t_cnt, t_off, t_tau, base_s);
 }
 
-// 32 < E <= 128: the approximate logits of GT_M tokens x all experts in one
+// 64 < E <= 128: the approximate logits of GT_M tokens x all experts in one
 // workgroup of 8 wavefronts, then the candidate pass, without the logits
 // leaving LDS.  The operands stream through an LDS ring of GT_NS stages of
 // 64-deep k-steps by direct global->LDS loads (8 lanes fetch one row's 128

@@ -501,13 +501,14 @@ __device__ __forceinline__ void store_f32(const Acc& acc, float* out, int ldo, i
 // in the same order, so y has the same bits.  Wave w multiplies row block w
 // (32 rows) by both 32-column blocks; every wave loads.  A ring stage holds
 // THIN_KS k-steps while the tile has at most 64 rows (16 KiB of weights per
-// stage, as much in flight as the wide tile: a CU's stream is bound by the
-// bytes it has in flight, 48 KiB a microsecond), else one.  A tile has about
-// 6 us of fixed cost (first loads, epilogue, claim), so it pays only where
-// whole slabs fill half the CUs or fewer: routing and layer of 32 decode tokens of a
-// fine-grained layer (54 and 72 whole-slab tiles) 91 us with them, 84 us with
-// narrow ones.  The weights of the first stages are loaded before the wait for
-// the tile's inputs.
+// stage, as much in flight as the wide tile), else one.  A narrow tile streams
+// slower than a wide one (traced: 0.26 MB of weights in 15.8 us where 216 run
+// together, 0.46 MB in 22 us of 512 on 256 workers; wide ones 1.05 MB in 43 us
+// of 198, 2.1 MB in 82 us of 224): its products wait for their LDS reads one
+// by one (compute).  So it pays only where whole slabs fill half the CUs or
+// fewer: routing and layer of 32 decode tokens of a fine-grained layer (54 and
+// 72 whole-slab tiles) 91 us with them, 84 us with narrow ones.  The weights of
+// the first stages are loaded before the wait for the tile's inputs.
 // ---------------------------------------------------------------------------
 constexpr int THIN_KS = 4, THIN_ROWS = 64;
 
@@ -534,7 +535,7 @@ __device__ __forceinline__ bool mainloop_thin_n(AccThin& acc, const AThin& A, co
   const int nk = Kd / KSTEP, ns = (nk + KS - 1) / KS;
   // this wave's DMA: k-step ks of a stage, A row block arb, B instructions
   const int ks = KS == 1 ? 0 : wave >> 1, arb = KS == 1 ? wave : wave & 1;
-  constexpr int BI = KS == 1 ? 1 : 2;             // B instructions (KS = 1: of waves 0-3)
+  constexpr int BI = KS == 1 ? 1 : 2;             // B instructions (KS = 1: waves 4-7 repeat those of waves 0-3)
   const int b0 = KS == 1 ? wave & 3 : (wave & 1) * 2;
   uint32_t oa[2], ob[BI];
 #pragma unroll
@@ -570,8 +571,9 @@ __device__ __forceinline__ bool mainloop_thin_n(AccThin& acc, const AThin& A, co
     fa[kk] = (uint32_t)swz(ra, c) * 16u;
     fb[kk] = (uint32_t)(A_ST + swz(lane & 31, c) * 16);
   }
-  // a whole stage: every fragment is read before the first product, so the
-  // one wave of a row block waits out the LDS latency once per stage
+  // a whole stage.  The compiled loop reads each fragment right before the
+  // product that takes it, whatever the order here, and the row block has one
+  // wave: it waits out the LDS latency before every product, 4 KS times a stage
   auto compute = [&](int s) {
     const char* st = ring + (s & (NSTAGE - 1)) * ST;
     bf16x8_t av[2 * KS], bv[2 * KS][NB];

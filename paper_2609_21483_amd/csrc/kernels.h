@@ -163,7 +163,7 @@ struct FwdArgs {
   int T, Tr, H, F, k, El, S, e0;
   int nt0, nt1;   // column tiles of GEMM0 (over 2F) and GEMM1 (over H); layers of few rows: Sched::nt counts, nt1 at most
   int gather;     // GEMM0 reads the routed rows straight from x and does not wait for their dispatch (few rows
-                  // per expert; not in the separate kernels)
+                  // per expert; not in the separate kernels): the movement workers fill A, nothing in the launch reads it
   int nsplit;     // split-K factor of GEMM1 (1, 2, 4 or 8)
   int dt, ct;     // tokens per dispatch unit (<= DT) and per combine unit (<= CT)
   int move_steal; // compute workers copy dispatch units while their rows are not

@@ -429,10 +429,10 @@ __global__ void __launch_bounds__(TBN + WAVE) tab_build_kernel(TableArgs a) {
     if (lane == 0) base[ki][K] = carry;
     wave_lds_sync();
     static_assert(NLVL == 1, "shared row tiles (level 0), then the routed ones");
-    // A layer of few rows takes the time of streaming its experts' weights.  A
-    // CU streams up to 47 GB/s and all of them together 5.9 TB/s, so whole-slab
-    // tiles for half the workers about fill HBM; fewer leave it idle, and
-    // narrow tiles do better in spite of their 6 us of fixed cost each.
+    // A layer of few rows takes the time of streaming its experts' weights.
+    // Whole-slab tiles stream 25 to 29 GB/s each (224 of them together 5.7
+    // TB/s, 144 of them 4.2), so with few of them HBM idles, and narrow tiles
+    // do better although one streams 17 to 21 GB/s only.
     // Routing and layer, whole slabs / narrow tiles: GEMM1 of 128 tiles on 256
     // workers 210 / 199 us; GEMM1 of 144 tiles 127 / 133 us.  Tiles of more
     // rows than a narrow one takes in its fast form (a skewed routing) pay only
