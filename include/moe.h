@@ -291,7 +291,7 @@ moe_status moe_route(moe_handle* h, const uint16_t* x, const uint16_t* wg,
  * x: bf16 [T][H], wg: bf16 [H][E], logit_bias: fp32 [E] or NULL; writes
  * topk_idx int32 [T][top_k] and topk_w fp32 [T][top_k] as moe_route does.
  * The gate's scratch (a copy of wg where E is no multiple of 4, and of wg or
- * x where they start off a 16-byte boundary; for large batches of more than 64
+ * x where they start off a 16-byte boundary; for large batches of more than 32
  * experts, intermediate logits, norms and candidate chains) lives in a static
  * device array of MOE_ROUTE_STATIC_SCRATCH_BYTES that each GPU the library
  * runs on holds until the process ends; problems of more than about

@@ -2,7 +2,7 @@
 // (token, expert) chain (gate.hip) costs more than finding the few that can
 // change the routing: the same defined logits (fp32, one accumulator, h
 // ascending, each product rounded before the add, then + bias), so the same
-// ids and weights.  E > 64 (gate_filtered).
+// ids and weights.  E > 32 (gate_filtered).
 //   1. gate_prep:  WgT = Wg transposed ([E][H]) and ||w_e||_2.
 //   2. gate_tile2 (E > 128: gate_tile): approximate logits L~ by bf16 MFMA (fp32 accumulation) and
 //      ||x_g||_2, then the candidates: a bound d_e >= |L - L~| (from the
@@ -339,7 +339,7 @@ __global__ void __launch_bounds__(NTH) gate_tile_kernel(FilterArgs a) {
   cand_tile<EPL>(a, g0, GT_M, t_cnt, t_off, t_tau, base_s);
 }
 
-// 64 < E <= 128: the approximate logits of GT_M tokens x all experts in one
+// 32 < E <= 128: the approximate logits of GT_M tokens x all experts in one
 // workgroup of 8 wavefronts, then the candidate pass, without the logits
 // leaving LDS.  The operands stream through an LDS ring of GT_NS stages of
 // 64-deep k-steps by direct global->LDS loads (8 lanes fetch one row's 128
@@ -922,14 +922,16 @@ __global__ void __launch_bounds__(NTH) gate_final_kernel(FilterArgs a) {
 // floor of 27 to 170 us.  The gate's time is a step function of T (rounds of
 // workgroups over the CUs, each a whole chain of H steps) and depends on E by
 // its class only, so the line between them is none of T * H: E = 128, k = 4,
-// H = 4096, gate : filter, us, 8192 tokens 92 : 129, 8200 156 : 130, 16384
-// 161 : 144, 16400 230 : 170; E = 260, k = 8, 16384 tokens 684 : 461; E = 130,
-// k = 2, 324 : 200; E = 256, k = 8, 10000 tokens 238 : 349.  So both times are
-// estimated (us) by formulas fitted to 25000 measured points (E 66 to 512, T
-// 512 to 131072, H 256 to 16384, k 1 to 8), and the smaller one decides: over
-// these points the choice is 0.2% slower than the better gate on average, by
-// more than 10% at 0.4% of them and by a third at most (H = 16384).  Up to 64
-// experts the gate was the faster one everywhere.
+// H = 4096, gate : filter, us, 8192 tokens 99 : 115, 8200 155 : 115, 512 (k =
+// 8) 49 : 111; E = 300, k = 8, 16384 tokens 678 : 446; E = 130, k = 2, 10000
+// tokens 245 : 167; E = 256, k = 8, 254 : 326; E = 85, k = 3, H = 8192, 9722
+// tokens 310 : 215; E = 54, k = 4, H = 3072, 50407 tokens 250 : 174.  So both
+// times are estimated (us) by formulas fitted to 20000 measured points of any
+// H (E 33 to 512, T 1500 to 160000, H 256 to 16384, k 1 to 8), and the smaller
+// one decides: over these points the choice is 0.24% slower than the better
+// gate on average, by more than 3% at 2.4% of them and by more than 10% at 0.8%
+// (k = 1, where the chains' time depends most on H).  Up to 32 experts there is
+// no filter that keeps up with the gate.
 static double gate_us(long long T, long long H, int E, int k) {
   const GateGeometry g = gate_geometry((int)T, E);
   const int cus = GATE_SIMDS / 4, wide = g.ec > 256;
@@ -944,31 +946,36 @@ static double gate_us(long long T, long long H, int E, int k) {
 
 static double filter_us(long long T, long long H, int E, int k) {
   struct Coef {
-    double t64, t64h, t128, t128h;  // a round of tiles of 64 or 128 tokens: fixed, per H
     double c, ck;                   // four launches; per expert chosen
-    double floor, chain;            // the chains: one of H steps; per 1e6 T k H, whichever is longer
-    double te, tk;                  // logits and candidates, per 1e6 T E; per 1e6 T k
-    double h4, h4tk, h8, h8tk;      // per 1000 H past 4096 and past 8192 (the chains' rows outgrow the L2s), the
-                                    // second of each also per 1e6 T k
+    double h, eh;                   // per 1000 H; per 1000 H and 128 experts
+    double t64, t64h, t128, t128h;  // a round of tiles of 64 or 128 tokens and a pass over 128 experts: fixed, per 1000 H
+    double floor, floor8;           // one chain, per 1000 H; per 1000 H past 8192
+    double ch[4];                   // or, if longer, the chains per 1e6 T k and 1000 H up to 4096, 8192, 12288 and past
+                                    // them (their rows outgrow the L2s)
+    double tk, te;                  // per 1e6 T k; logits and candidates, per 1e6 T E
   };
   static const Coef coef[3] = {
-      {-2.0, 0.015, -1.3, 0.0232, 25.6, -1.64, 0.0031, 0.388, 3.32, 35, 17.2, 161, 19.1, 607},  // E <= 128, k < 4
-      {0.95, 0.0119, 1.7, 0.0182, 16.7, 0.99, 0.0133, 0.103, 3.28, 17.5, -4.9, 130, -2.3, 210},  // E <= 128, k >= 4
-      {11.1, 0.0095, 26.2, 0.018, 28.4, 3.3, 0, 0.411, 6.0, 187, 17.4, 204, 24.2, 1540}};
-  const Coef& c = coef[E > 128 ? 2 : k >= 4 ? 1 : 0];
-  const double h = (double)H, tk = 1e-6 * (double)T * k, te = 1e-6 * (double)T * E, passes = (E + 127) / 128;
+      {16.25, -1.11, 0.64, 3.44, 4.22, 11.99, 5.96, 20.54, 1.72, 37.44, {274.57, 786.57, 1306.32, 3028.25}, 86.75, 1.22},
+      {12.93, 0.43, 5.98, 4.89, 6.24, 7.05, 8.27, 13.18, 5.56, 1.53, {75.12, 125.54, 218.17, 404.92}, 28.17, 0.65},
+      {8.9, 2.67, 8.18, 0.78, 14.95, 7.51, 30.78, 15.39, -10.39, 72.34, {319.96, 657.61, 1412.23, 3470.62}, 246.02, 4.39}};
+  const Coef& c = coef[E > 128 ? 2 : k >= 4 ? 1 : 0];  // (gate_chain, E <= 128; gate_chain_staged; E > 128)
+  const double h = 1e-3 * (double)H, tk = 1e-6 * (double)T * k, te = 1e-6 * (double)T * E;
   const long long big = 128 * 256;
   const double tiles = T < big ? (double)((2 * T + big - 1) / big) * (c.t64 + c.t64h * h)
                                : (double)((T + big - 1) / big) * (c.t128 + c.t128h * h);
-  const double floor = c.floor * h, chains = c.chain * tk * h;
-  const double h4 = H > 4096 ? 1e-3 * (h - 4096) : 0, h8 = H > 8192 ? 1e-3 * (h - 8192) : 0;
-  return c.c + c.ck * k + tiles * passes + (floor > chains ? floor : chains) + c.te * te + c.tk * tk +
-         h4 * (c.h4 + c.h4tk * tk) + h8 * (c.h8 + c.h8tk * tk);
+  double chains = 0;
+  for (int i = 0; i < 4; ++i) {
+    const double past = h - 4.096 * i;
+    if (past > 0) chains += tk * c.ch[i] * (i < 3 && past > 4.096 ? 4.096 : past);
+  }
+  const double floor = c.floor * h + (h > 8.192 ? c.floor8 * (h - 8.192) : 0);
+  return c.c + c.ck * k + c.h * h + c.eh * h * E / 128 + tiles * ((E + 127) / 128) + (floor > chains ? floor : chains) +
+         c.tk * tk + c.te * te;
 }
 
 bool gate_filtered(long long T, long long H, int E, int k) {
   // (the chain list is indexed with 32 bits)
-  return E > 64 && T * E < (1LL << 31) && filter_us(T, H, E, k) < gate_us(T, H, E, k);
+  return E > 32 && T * E < (1LL << 31) && filter_us(T, H, E, k) < gate_us(T, H, E, k);
 }
 
 // the filter's kernels in order on `s`

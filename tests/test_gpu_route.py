@@ -288,6 +288,7 @@ def test_gate_classes(B, T, H, E, k, bias):
 # tokens, E <= 128 and above, and chains k < 4, k < 8, k = 8
 FILTER_GATES = [(8200, 832, 66, 1, False), (8300, 1088, 100, 6, True), (8200, 1216, 66, 8, True),
                 (33000, 512, 66, 1, True), (32800, 384, 66, 4, False), (33000, 448, 66, 8, False),
+                (8200, 2880, 34, 1, True), (16600, 1728, 48, 4, False), (16700, 1920, 64, 4, True),  # 33 to 64 experts
                 (4100, 1472, 257, 2, True), (8300, 2048, 300, 8, False), (41000, 1600, 129, 1, True)]
 
 
