@@ -505,10 +505,10 @@ __device__ __forceinline__ void store_f32(const Acc& acc, float* out, int ldo, i
 // slower than a wide one (traced: 0.26 MB of weights in 15.8 us where 216 run
 // together, 0.46 MB in 22 us of 512 on 256 workers; wide ones 1.05 MB in 43 us
 // of 198, 2.1 MB in 82 us of 224): its products wait for their LDS reads one
-// by one (compute).  So it pays only where whole slabs fill half the CUs or
-// fewer: routing and layer of 32 decode tokens of a fine-grained layer (54 and
-// 72 whole-slab tiles) 91 us with them, 84 us with narrow ones.  The weights of
-// the first stages are loaded before the wait for the tile's inputs.
+// by one (compute).  So it pays only where whole slabs leave CUs idle, and not
+// in shallow GEMM0s (the rule, with its measurements, is the table builder's).
+// The weights of the first stages are loaded before the wait for the tile's
+// inputs.
 // ---------------------------------------------------------------------------
 constexpr int THIN_KS = 4, THIN_ROWS = 64;
 

@@ -432,14 +432,19 @@ __global__ void __launch_bounds__(TBN + WAVE) tab_build_kernel(TableArgs a) {
     // A layer of few rows takes the time of streaming its experts' weights.
     // Whole-slab tiles stream 25 to 29 GB/s each (224 of them together 5.7
     // TB/s, 144 of them 4.2), so with few of them HBM idles, and narrow tiles
-    // do better although one streams 17 to 21 GB/s only.
-    // Routing and layer, whole slabs / narrow tiles: GEMM1 of 128 tiles on 256
-    // workers 210 / 199 us; GEMM1 of 144 tiles 127 / 133 us.  Tiles of more
-    // rows than a narrow one takes in its fast form (a skewed routing) pay only
-    // while every worker has at most one: of 256 rows each (H = 2048), 8 row
-    // tiles 117 / 92 us, 16 of them 123 / 143.
-    const int per = offs[El] + a.S * a.Tr > gemm::THIN_ROWS * carry ? BN / THIN_N : 2;
-    const bool thin0 = a.few && carry * a.wide0 * per <= a.N, thin1 = a.few && carry * a.wide1 * per <= a.N;
+    // do better, although one streams 17 to 21 GB/s only, if the phase is deep
+    // enough for their fixed cost.  Narrow against whole slabs on 256 workers,
+    // weights from HBM, time of the layer over 900 random shapes and routings
+    // (geometric means) by the number m of narrow tiles:
+    //   GEMM0: H to 512 0.97 to 1.24; to 1024 1.08 up to m = 16, then 0.92 to 0.96 up
+    //   to 256, 1.02 to 1.17 above; to 1536 1.03 (0.82 for m = 14 to 16), 0.86 to
+    //   0.92, 0.98 to 1.08; past 1536 0.69 to 0.99 up to m = 512, 1.01 to 1.09 above.
+    //   GEMM1 by the depth of a split: to 128 0.96 to 1.00 up to m = 128, 1.00 to
+    //   1.17 above; to 512 0.92 to 1.01 up to 256, 1.02 to 1.17 above; past 512 0.72
+    //   to 1.00 up to 512, 0.98 to 1.13 above.
+    const int m0 = carry * ceil_div(2 * a.F, THIN_N), m1 = carry * ceil_div(a.H, THIN_N) * a.nsplit, d1 = a.F / a.nsplit;
+    const bool thin0 = a.few && (a.H > 1536 ? m0 <= 2 * a.N : a.H > 512 && m0 > a.N / (a.H > 1024 ? 32 : 16) && m0 <= a.N);
+    const bool thin1 = a.few && m1 <= (d1 > 512 ? 2 * a.N : d1 > 128 ? a.N : a.N / 2);
     const int nt0 = thin0 ? ceil_div(2 * a.F, THIN_N) : a.wide0;
     const int nt1 = thin1 ? ceil_div(a.H, THIN_N) : ceil_div(a.H, BN);
 #pragma unroll 1

@@ -144,15 +144,21 @@ def test_gemm1_split_factors(B, split):
 
 
 @pytest.mark.parametrize("shape,skew,split", [
+    # GEMM0 in whole slabs, GEMM1 in narrow tiles
     (W.MoeShape("few32", 90, 2, 40, 192, 192, 16, 2, 4), 0, 1),           # one row block, ragged columns
     (W.MoeShape("few64", 89, 3, 64, 128, 192, 8, 2, 8, n_shared_experts=1), 0, 2),  # two; rank 0 fills a shared one
     (W.MoeShape("few_skew", 88, 2, 192, 128, 320, 32, 4, 6), 1, 1),      # one expert takes every token: 256 rows + 128
-    (W.MoeShape("few_wide", 87, 1, 64, 128, 512, 48, 8, 40), 0, 4),      # GEMM0 in whole slabs, GEMM1 in narrow tiles
-    (W.MoeShape("few_wide_skew", 86, 1, 384, 320, 512, 64, 8, 48), 1, 1),
+    (W.MoeShape("few_wide", 87, 1, 64, 128, 512, 48, 8, 40), 0, 4),      # both in whole slabs
+    (W.MoeShape("few_wide_skew", 86, 1, 384, 320, 512, 64, 8, 48), 1, 1),  # GEMM1 in narrow tiles, two of them tall
+    # GEMM0 deep enough for narrow tiles
+    (W.MoeShape("few_deep32", 69, 2, 40, 1536, 192, 16, 2, 8), 0, 1),
+    (W.MoeShape("few_deep64", 68, 3, 64, 1600, 192, 8, 2, 8, n_shared_experts=1), 0, 2),
+    (W.MoeShape("few_deep_skew", 67, 2, 192, 1536, 320, 32, 4, 6), 1, 1),
+    (W.MoeShape("few_deep_two", 66, 1, 16, 4096, 512, 24, 2, 24), 0, 1),  # more of them than workers
 ], ids=lambda v: getattr(v, "name", None))
 def test_few_rows(B, shape, skew, split):
     """Layers of at most 48 routed rows per expert gather their rows and run
-    phases of few tiles in narrow ones: y matches the oracle and has the bits
+    phases of few tiles in narrow ones (GEMM0 where it is deep): y matches the oracle and has the bits
     of the general path, which a layer of the same tokens and routing several
     times over takes (a token's y does not depend on the other tokens)."""
     shape = shape.with_(w_std=0.05)
@@ -191,8 +197,9 @@ def test_few_rows(B, shape, skew, split):
 
 
 @pytest.mark.parametrize("shape,spread,split", [
-    (W.MoeShape("few_units3", 81, 1, 770, 128, 1088, 17, 1, 8), 8, 1),     # tall row tiles, too many for narrow ones
-    (W.MoeShape("few_units3n", 80, 1, 770, 128, 960, 17, 1, 8), 8, 2),     # tall row tiles, narrow
+    (W.MoeShape("few_units3", 81, 1, 770, 128, 1088, 17, 1, 8), 8, 1),     # tall row tiles, GEMM0 in whole slabs
+    (W.MoeShape("few_units3n", 80, 1, 770, 128, 960, 17, 1, 8), 8, 2),     # and GEMM1 in two splits
+    (W.MoeShape("few_units3d", 62, 1, 770, 1536, 960, 17, 1, 8), 8, 1),    # tall row tiles, narrow in both
     (W.MoeShape("few_units4", 79, 2, 513, 192, 192, 86, 4, 20), 86, 1),    # dispatch units of 4 tokens, the last of 2
     (W.MoeShape("few_units8", 78, 1, 4096, 64, 128, 86, 1, 3), 3, 1),      # the most tokens that gather, all local
     (W.MoeShape("beyond_few", 77, 1, 4097, 64, 128, 86, 1, 3), 3, 1),      # one more
@@ -217,6 +224,7 @@ def test_few_rows_under_skewed_routing(B, shape, spread, split):
 
 @pytest.mark.parametrize("shape", [W.MoeShape("view_few", 76, 2, 40, 192, 192, 16, 2, 4),
                                    W.MoeShape("view_few_wide", 75, 1, 64, 128, 512, 48, 8, 40),
+                                   W.MoeShape("view_few_deep", 63, 2, 40, 1536, 192, 16, 2, 8),
                                    W.MoeShape("view_general", 74, 2, 300, 128, 192, 4, 2, 2)], ids=lambda s: s.name)
 @pytest.mark.parametrize("off", [1, 4])
 def test_tokens_off_a_16_byte_boundary(B, shape, off):
@@ -353,9 +361,11 @@ def test_run_stages_reproduces_forward(B, K):
 
 
 @pytest.mark.parametrize("shape", [
-    W.MoeShape("few_stages", 85, 2, 40, 192, 192, 16, 2, 4),          # narrow tiles of one row block
-    W.MoeShape("few_stages_wide", 84, 1, 64, 128, 512, 48, 8, 40),    # GEMM0 in whole slabs
+    W.MoeShape("few_stages", 85, 2, 40, 192, 192, 16, 2, 4),          # GEMM1 in narrow tiles of one row block
+    W.MoeShape("few_stages_wide", 84, 1, 64, 128, 512, 48, 8, 40),    # whole slabs
     W.MoeShape("few_stages_tall", 83, 2, 192, 128, 320, 16, 1, 1),    # one expert of many rows: one k-step a stage
+    W.MoeShape("few_deep", 65, 2, 40, 1536, 192, 16, 2, 8),           # GEMM0 in narrow tiles too
+    W.MoeShape("few_deep_tall", 64, 2, 192, 1536, 704, 16, 1, 1),
     W.MoeShape("general_stages", 82, 2, 300, 128, 192, 4, 2, 2),
 ], ids=lambda s: s.name)
 @pytest.mark.parametrize("K", [1, 4])
@@ -364,7 +374,7 @@ def test_run_stages_read_what_earlier_stages_wrote(B, shape, K):
     GEMM0 reads the dispatched rows, also in layers of few rows."""
     c = make_case(shape.with_(w_std=0.05))
     idx, w = W.random_routing(shape.T, shape.n_experts, shape.top_k, seed=11)
-    if shape.name == "few_stages_tall":
+    if shape.name.endswith("tall"):
         idx[:] = 0
     idx, w = idx.astype(np.int32), w.astype(np.float32)
     ml = B.MoeLayer(shape, c.w1, c.w3, c.w2)

@@ -68,17 +68,18 @@ def test_stack_matches_single_launches_and_oracle(B, shape, n_layers, mode):
             ml.close()
 
 
+@pytest.mark.parametrize("H", [128, 1536])  # GEMM0 of the narrow layer in whole slabs, in narrow tiles
 @pytest.mark.parametrize("plan", [None, (8, 2, 3, 1)], ids=["model", "K2"])
-def test_stack_of_few_row_layers(B, plan):
+def test_stack_of_few_row_layers(B, plan, H):
     """A stack that holds a layer of few rows runs the few-row kernel for all
     of its layers: narrow tiles, whole slabs of gathered rows, and a general
     layer between them give the bits of their single launches."""
-    shapes = [W.MoeShape(n, 80 + i, 2, 64, 128, F, E, 2, E, w_std=0.05)
+    shapes = [W.MoeShape(n, 80 + i, 2, 64, H, F, E, 2, E, w_std=0.05)
               for i, (n, F, E) in enumerate([("narrow", 64, 32), ("general", 192, 4), ("slabs", 640, 32)])]
     cases = [make_case(s) for s in shapes]
     layers = [B.MoeLayer(s, c.w1, c.w3, c.w2) for s, c in zip(shapes, cases)]
     try:
-        T, H = shapes[0].T, shapes[0].hidden
+        T = shapes[0].T
         x = cases[0].x.cuda()
         forced = None if plan is None else B.moe_plan(*plan, 0.0)
         idx, w, singles = [], [], []
