@@ -200,7 +200,8 @@ def test_few_rows(B, shape, skew, split):
     (W.MoeShape("few_units3", 81, 1, 770, 128, 1088, 17, 1, 8), 8, 1),     # tall row tiles, GEMM0 in whole slabs
     (W.MoeShape("few_units3n", 80, 1, 770, 128, 960, 17, 1, 8), 8, 2),     # and GEMM1 in two splits
     (W.MoeShape("few_units3d", 62, 1, 770, 1536, 960, 17, 1, 8), 8, 1),    # tall row tiles, narrow in both
-    (W.MoeShape("few_units4", 79, 2, 513, 192, 192, 86, 4, 20), 86, 1),    # dispatch units of 4 tokens, the last of 2
+    (W.MoeShape("few_units4", 79, 2, 513, 192, 192, 86, 4, 20), 86, 1),    # dispatch units of 8 tokens, the last of 2
+    (W.MoeShape("few_units3t", 61, 2, 83, 192, 192, 24, 4, 20), 24, 1),    # of 3 tokens, the last of 1
     (W.MoeShape("few_units8", 78, 1, 4096, 64, 128, 86, 1, 3), 3, 1),      # the most tokens that gather, all local
     (W.MoeShape("beyond_few", 77, 1, 4097, 64, 128, 86, 1, 3), 3, 1),      # one more
 ], ids=lambda v: getattr(v, "name", None))
